@@ -127,9 +127,14 @@ int tile_lines(int n) { return n >= 1024 ? 1 : 1024 / n; }
 
 // Lines per block: the default tile, halved while the grid would have fewer than `target`
 // blocks. Small blocks keep the barrier rounds of a wall-normal pass cheap and let several
-// blocks interleave on a CU; 2D grids have only nx/2 + 1 lines.
-int spread_lines(int tl, int lines, int target) {
-  while (tl > 1 && (lines + tl - 1) / tl < target) tl >>= 1;
+// blocks interleave on a CU; 2D grids have only nx/2 + 1 lines. Once every CU has a block
+// (256), a block keeps at least a wavefront (per_line: threads per line): a block of 4 threads
+// still occupies a wavefront, so splitting on only multiplies the wavefronts and shortens the
+// row pieces that a load reads (32 x 32 x 16 coarse cells, FP32: zpass_ch 2112 blocks of 4
+// threads 11.7 us, the step 107 -> 103 us).
+int spread_lines(int tl, int lines, int target, int per_line) {
+  auto blocks = [&] { return (lines + tl - 1) / tl; };
+  while (tl > 1 && blocks() < target && (tl * per_line > 64 || blocks() < 256)) tl >>= 1;
   return tl;
 }
 
@@ -796,7 +801,7 @@ template <typename T>
 hipError_t launch_zpass_helmholtz(const Dims& d, const Tables<T>& tb, cx<T>* spec, int bc,
                                   double coeff, double shift, double scale, hipStream_t st) {
   const int lines = d.lines();
-  const int TL = spread_lines(tile_lines(d.nz), lines, 2048);
+  const int TL = spread_lines(tile_lines(d.nz), lines, 2048, d.nz);
   const size_t shm = pcr_sym_bytes<double, 1, 1>(d.nz, TL);
   hipLaunchKernelGGL(k_zpass_helmholtz<T>, dim3((lines + TL - 1) / TL), dim3(TL * d.nz), shm, st, spec,
                      d.pitch, d.ny, d.nz, tb.lam_x, tb.lam_y, 1.0 / (d.hz * d.hz), bc, coeff, shift,
@@ -833,7 +838,7 @@ hipError_t launch_zpass_ch(const Dims& d, const Tables<T>& tb, cx<T>* spec, doub
     // tiles of 128 bytes per row (8 complex FP64 modes): one cache line
     int TL = (int)(128 / sizeof(cx<T>));
     while (TL > 1 && TL * d.nz > 4096) TL >>= 1;
-    TL = spread_lines(TL, d.lines(), 2048);
+    TL = spread_lines(TL, d.lines(), 2048, d.nz >= 4 ? d.nz / 4 : 1);
     int threads = TL * (d.nz >= 4 ? d.nz / 4 : 1);
     threads = ((threads + 63) / 64) * 64;
     if (threads > 1024) threads = 1024;
@@ -865,7 +870,7 @@ hipError_t launch_zpass_ch(const Dims& d, const Tables<T>& tb, cx<T>* spec, doub
     int TL = 16;
     const int per_line = d.nz > (1 << fft_lp<T>()) ? d.nz >> fft_lp<T>() : 1;
     while (TL > 1 && (TL * d.nz > 4096 || TL * per_line > kZBlock)) TL >>= 1;
-    TL = spread_lines(TL, d.lines(), 2048);
+    TL = spread_lines(TL, d.lines(), 2048, per_line);
     const int lines = d.lines();
     const int threads = TL * per_line;
     // the inverse transforms are unnormalised: fold 1/nz into the spectral scale
@@ -901,7 +906,7 @@ hipError_t launch_zpass_ns(const Dims& d, const Tables<T>& tb, cx<T>* spec4, con
   // at most 64 KB of LDS per block (the FP64 form of a 1024-thread block would need 96 KB)
   int TL = tile_lines(d.nz);
   while (TL > 1 && shm_of(TL) > 65536) TL >>= 1;
-  TL = spread_lines(TL, lines, 2048);
+  TL = spread_lines(TL, lines, 2048, d.nz);
   const double bw = -2.0 * c.nu_m / (d.hz * d.hz);
   const double4 wall = make_double4(bw * c.uwb[0], bw * c.uwt[0], bw * c.uwb[1], bw * c.uwt[1]);
   // FP32: registers for two blocks of 1024 threads per CU; FP64 (whose LDS allows one such
@@ -923,7 +928,7 @@ hipError_t launch_zpass_ns_adj(const Dims& d, const Tables<double>& tb, cx<doubl
   // at most 64 KB of LDS per block, as in the forward pass
   int TL = tile_lines(d.nz);
   while (TL > 1 && shm_of(TL) > 65536) TL >>= 1;
-  TL = spread_lines(TL, lines, 2048);
+  TL = spread_lines(TL, lines, 2048, d.nz);
   const size_t shm = shm_of(TL);
   hipLaunchKernelGGL(k_zpass_ns_adj, dim3((lines + TL - 1) / TL), dim3(TL * d.nz), shm, st, spec4, d.pitch,
                      d.ny, d.nz, tb.lam_x, tb.lam_y, tb.ph_x, tb.ph_y, 1.0 / d.hx, 1.0 / d.hy, 1.0 / d.hz,
