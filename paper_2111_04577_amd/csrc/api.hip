@@ -211,9 +211,10 @@ struct drpf_grid {
   Offsets o;
   // adjoint workspace (FP64 grids), attached by drpf_adjoint_attach
   char* aws = nullptr;
-  // viscoelastic grids: the polymer update of a step runs on a stream of the library's own,
-  // forked from the caller's stream after the velocity correction and joined before the next
-  // step's momentum right-hand side (the next step's Cahn-Hilliard pass overlaps it)
+  // log-conformation grids: the polymer update of a step that another step of the same call
+  // follows runs on a stream of the library's own, forked from the caller's stream after the
+  // velocity correction and joined before the next step's momentum right-hand side (the next
+  // step's Cahn-Hilliard pass overlaps it)
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   bool pending = false;
@@ -556,9 +557,15 @@ template <typename T>
 int step_impl(drpf_grid* g, drpf_state* s, int nsteps, hipStream_t st) {
   const bool ve = g->p.viscoelastic != 0;
   const int every = g->p.check_finite_every;
-  // the polymer update overlaps the next step on the library's stream, except while per-kernel
-  // events are being recorded (they time one stream)
-  const bool overlap = g->side != nullptr && !g->prof;
+  // The log-conformation update, which is bound by arithmetic, overlaps the next step's
+  // Cahn-Hilliard pass, which is bound by memory (except while per-kernel events are being
+  // recorded: they time one stream). A fork and join costs about 25 us of host time and two
+  // queue hand-overs, so it is not made for the last step of a call, where nothing follows to
+  // overlap with, nor for the stress form, whose update is bound by memory too. Eight steps with
+  // and without it, 128 x 128 x 64 coarse cells, log-conformation with WENO-Z: 5.41 / 6.07 ms FP32,
+  // 9.44 / 10.04 ms FP64; 256 x 256 x 128, stress form: 16.85 / 16.81 and 31.8 / 31.7 ms; one step
+  // of the former 0.780 / 0.759 ms, four steps of 32 x 32 x 16, stress form: 0.385 / 0.343 ms.
+  const bool can_overlap = g->side != nullptr && !g->prof;
   // whatever happens, the caller's stream ends up after the last polymer update
   struct Join {
     drpf_grid* g;
@@ -572,7 +579,7 @@ int step_impl(drpf_grid* g, drpf_state* s, int nsteps, hipStream_t st) {
   } join{g, st};
   for (int n = 0; n < nsteps; ++n) {
     const StepConsts& K = s->step == 0 ? g->k1 : g->k2;
-    const int rc = step_one<T>(g, state_io<T>(s), K, st, overlap);
+    const int rc = step_one<T>(g, state_io<T>(s), K, st, can_overlap && n + 1 < nsteps);
     if (rc) return rc;
     // ---- rotate time levels (pointer swaps only)
     void* ph0 = s->phi[0];
@@ -1001,7 +1008,7 @@ int drpf_init_grid(const drpf_params* p, void* d_workspace, size_t bytes, void* 
     void* scr = nullptr;
     rc = scratch_ptr(&scr);
   }
-  if (!rc && p->viscoelastic) {
+  if (!rc && p->viscoelastic && p->constitutive == 1) {
     // the stream the polymer update overlaps on (default priority) and its fork/join events
     hipError_t e = hipStreamCreateWithFlags(&g->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&g->ev_fork, hipEventDisableTiming);
