@@ -70,7 +70,7 @@ __device__ __forceinline__ void cell_index(int& k, int& j, int& i) {
 }
 
 // ---- WENO-Z advection transposed (advection 1, Sec. 3.2.3) ---------------------------------
-// The face value of weno_face (stencil v[0..4] = the five upwind cells, the face between v[2]
+// The face value of weno_face_div (stencil v[0..4] = the five upwind cells, the face between v[2]
 // and v[3]) and its gradient g = d value / d v. value = sum a_k q_k / sum a_k, so
 // d value = sum (a_k dq_k + (q_k - value) da_k) / sum a_k, da_k = d_k (dt5 / (b_k + eps) -
 // t5 db_k / (b_k + eps)^2), t5 = |b_0 - b_2| with dt5 = sign(b_0 - b_2)(db_0 - db_2), taken as
@@ -165,7 +165,7 @@ template <bool PER, typename Q>
 __device__ __forceinline__ D weno_value(int f, int n, D uf, Q&& q) {
   int c[5];
   weno_cells<PER>(f, n, uf > 0.0, c);
-  return weno_face<D>(q(c[0]), q(c[1]), q(c[2]), q(c[3]), q(c[4]));
+  return weno_face_div<D>(q(c[0]), q(c[1]), q(c[2]), q(c[3]), q(c[4]));
 }
 
 // Transposed stress right-hand side for fixed velocity: out = (d RH / d tau)^T g, per cell.

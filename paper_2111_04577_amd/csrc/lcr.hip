@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(kBlock)
     double adv;
     if (WENO) {
       // WENO-Z face values, three cells either way, mirrored beyond the walls
-      adv = (double)wo.advection(thin.p[m], uxm, uxp, vym, vyp, wzm, wzp, ihx, ihy, ihz);
+      adv = (double)wo.template advection<false>(thin.p[m], uxm, uxp, vym, vyp, wzm, wzp, ihx, ihy, ihz);
     } else {
       const T* q = thin.p[m];
       const T fxp = uxp * h * (t0 + ld_at(q, no.xp));

@@ -513,6 +513,7 @@ __global__ void __launch_bounds__(256)
     k_weno_adv_zm(const T* __restrict__ phin, const T* __restrict__ phinm1, Prolonged<T> pv,
                   T* __restrict__ adv, int nx, int ny, int nz, int KB, T ihx, T ihy, T ihz) {
   extern __shared__ __align__(16) unsigned char smem[];
+  constexpr bool DIV = !Y3D && sizeof(T) == 8;  // see weno_face_div
   const int TX = blockDim.x, TY = blockDim.y;
   int bx, by, bz;
   xcd_tile(bx, by, bz);
@@ -535,7 +536,7 @@ __global__ void __launch_bounds__(256)
   T zw[8];  // phi* at K-4 .. K+3 of this column
 #pragma unroll
   for (int d = 0; d < 8; ++d) zw[d] = ps_at(mirror_index(K0 - 4 + d, nz), col);
-  T fbot = weno_flux(pv.wf(K0 - 1, J, I), zw[1], zw[2], zw[3], zw[4], zw[5], zw[6]);
+  T fbot = weno_flux<DIV>(pv.wf(K0 - 1, J, I), zw[1], zw[2], zw[3], zw[4], zw[5], zw[6]);
   // this thread's tile points and faces, the same on every layer: decomposed once (at most
   // NT tile points and two faces of each direction per thread; checked by the launcher)
   constexpr int NT = Y3D ? 4 : 2;
@@ -592,7 +593,7 @@ __global__ void __launch_bounds__(256)
       if (xr[q] >= 0) {
         const int r = xr[q], c = xc[q];
         const T* v = sT + (Y3D ? r + 3 : 0) * HX + c;  // cells X0 - 3 + c .. X0 + 2 + c
-        sFx[r * (TX + 1) + c] = weno_flux(xu[q], v[0], v[1], v[2], v[3], v[4], v[5]);
+        sFx[r * (TX + 1) + c] = weno_flux<DIV>(xu[q], v[0], v[1], v[2], v[3], v[4], v[5]);
       }
     }
     if (Y3D) {
@@ -601,11 +602,11 @@ __global__ void __launch_bounds__(256)
         if (yr[q] >= 0) {
           const int r = yr[q], c = yc[q];
           const T* v = sT + r * HX + c + 3;  // rows Y0 - 3 + r .. Y0 + 2 + r
-          sFy[r * TX + c] = weno_flux(yv[q], v[0], v[HX], v[2 * HX], v[3 * HX], v[4 * HX], v[5 * HX]);
+          sFy[r * TX + c] = weno_flux<DIV>(yv[q], v[0], v[HX], v[2 * HX], v[3 * HX], v[4 * HX], v[5 * HX]);
         }
       }
     }
-    const T ftop = weno_flux(pv.wf(K, J, I), zw[2], zw[3], zw[4], zw[5], zw[6], zw[7]);
+    const T ftop = weno_flux<DIV>(pv.wf(K, J, I), zw[2], zw[3], zw[4], zw[5], zw[6], zw[7]);
     __syncthreads();
     T d = (sFx[ty * (TX + 1) + tx + 1] - sFx[ty * (TX + 1) + tx]) * ihx + (ftop - fbot) * ihz;
     if (Y3D) d += (sFy[(ty + 1) * TX + tx] - sFy[ty * TX + tx]) * ihy;

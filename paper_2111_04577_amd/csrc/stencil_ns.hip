@@ -501,7 +501,8 @@ struct TauOut {
   T* p[6];
 };
 
-template <typename T, bool WENO>
+// DIV: the WENO-Z face values in the form of weno_face_div (2D FP64 grids).
+template <typename T, bool WENO, bool DIV = false>
 __global__ void __launch_bounds__(kBlock)
     k_polymer_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w,
                     TauSet<T> tn, TauSet<T> tin, TauOut<T> tout, int nx, int ny, int nz, T ihx,
@@ -533,7 +534,7 @@ __global__ void __launch_bounds__(kBlock)
     T rh;
     if (WENO) {
       // WENO-Z face values, three cells either way, mirrored beyond the walls
-      rh = wo.advection(tin.p[m], uxm, uxp, vym, vyp, wzm, wzp, ihx, ihy, ihz);
+      rh = wo.template advection<DIV>(tin.p[m], uxm, uxp, vym, vyp, wzm, wzp, ihx, ihy, ihz);
     } else {
       const T* q = tin.p[m];
       const T fxp = uxp * h * (t0 + ld_at(q, no.xp));
@@ -921,14 +922,16 @@ hipError_t launch_polymer_stage(const Dims& c, const StepConsts& k, const T* u, 
   const Launch3 L = launch3(c.nx, c.ny, c.nz);
   const T gk = (T)(k.giesekus == 0.0 ? 0.0 : k.giesekus / (1.0 - k.beta));
   const Walls<T> wl = walls_of<T>(k);
-  if (k.advection == 1)
-    hipLaunchKernelGGL((k_polymer_stage<T, true>), L.grid, L.block, 0, st, u, v, w, tn, ti, to, c.nx, c.ny,
-                       c.nz, (T)c.ihx, (T)c.ihy, (T)c.ihz, (T)k.dt, (T)k.inv_wi, (T)(1.0 - k.beta), gk, (T)c0,
-                       (T)c1, wl);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, L.grid, L.block, 0, st, u, v, w, tn, ti, to, c.nx, c.ny, c.nz, (T)c.ihx,
+                       (T)c.ihy, (T)c.ihz, (T)k.dt, (T)k.inv_wi, (T)(1.0 - k.beta), gk, (T)c0, (T)c1, wl);
+  };
+  if (k.advection != 1)
+    go(k_polymer_stage<T, false>);
+  else if (sizeof(T) == 8 && c.ny == 1)
+    go(k_polymer_stage<T, true, sizeof(T) == 8>);
   else
-    hipLaunchKernelGGL((k_polymer_stage<T, false>), L.grid, L.block, 0, st, u, v, w, tn, ti, to, c.nx, c.ny,
-                       c.nz, (T)c.ihx, (T)c.ihy, (T)c.ihz, (T)k.dt, (T)k.inv_wi, (T)(1.0 - k.beta), gk, (T)c0,
-                       (T)c1, wl);
+    go(k_polymer_stage<T, true>);
   return hipGetLastError();
 }
 

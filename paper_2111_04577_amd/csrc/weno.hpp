@@ -47,21 +47,55 @@ __device__ __forceinline__ T weno_face(T vm2, T vm1, T v0, T vp1, T vp2) {
   }
 }
 
+// a / b: exact in FP64; in FP32 through the hardware reciprocal (within 1 ulp of it), which
+// the FP32 form's round-off budget absorbs and which is several times cheaper than IEEE division.
+__device__ __forceinline__ double wdiv(double a, double b) { return a / b; }
+__device__ __forceinline__ float wdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
+
+// The same value with every quotient a division of its own: the form of the 2D FP64 kernels and
+// of the reverse pass. The reverse pass differentiates the weights; where the field is flat to
+// round-off their derivatives turn a change in the last bit of the forward values into 4e-7 of the
+// gradient, so gradient runs (2D, FP64) keep their forward arithmetic, and the reverse kernels the
+// arithmetic they differentiate. A 2D step is bound by launches and latency, not by this.
+template <typename T>
+__device__ __forceinline__ T weno_face_div(T vm2, T vm1, T v0, T vp1, T vp2) {
+  const T eps = sizeof(T) == 8 ? (T)1e-40 : (T)1e-30;
+  const T q0 = ((T)2 * vm2 - (T)7 * vm1 + (T)11 * v0) / (T)6;
+  const T q1 = (-vm1 + (T)5 * v0 + (T)2 * vp1) / (T)6;
+  const T q2 = ((T)2 * v0 + (T)5 * vp1 - vp2) / (T)6;
+  const T c13 = (T)(13.0 / 12.0), c14 = (T)0.25;
+  const T s0 = vm2 - (T)2 * vm1 + v0, r0 = vm2 - (T)4 * vm1 + (T)3 * v0;
+  const T s1 = vm1 - (T)2 * v0 + vp1, r1 = vm1 - vp1;
+  const T s2 = v0 - (T)2 * vp1 + vp2, r2 = (T)3 * v0 - (T)4 * vp1 + vp2;
+  const T b0 = c13 * (s0 * s0) + c14 * (r0 * r0);
+  const T b1 = c13 * (s1 * s1) + c14 * (r1 * r1);
+  const T b2 = c13 * (s2 * s2) + c14 * (r2 * r2);
+  const T t5 = fabs(b0 - b2);
+  const T a0 = (T)0.1 * ((T)1 + wdiv(t5, b0 + eps));
+  const T a1 = (T)0.6 * ((T)1 + wdiv(t5, b1 + eps));
+  const T a2 = (T)0.3 * ((T)1 + wdiv(t5, b2 + eps));
+  return wdiv(a0 * q0 + a1 * q1 + a2 * q2, a0 + a1 + a2);
+}
+
 // Flux u q at the face between cells c0 and p1, with q reconstructed on the upwind side from
 // the six cells m2, m1, c0, p1, p2, p3 around the face (a zero velocity carries no flux).
-// The stencil is picked by the sign first, so one reconstruction is evaluated, not two.
-template <typename T>
+// The stencil is picked by the sign first, so one reconstruction is evaluated, not two. DIV: in
+// the form of weno_face_div.
+template <bool DIV, typename T>
 __device__ __forceinline__ T weno_flux(T u, T m2, T m1, T c0, T p1, T p2, T p3) {
   const bool pos = u > (T)0;
-  return u * weno_face(pos ? m2 : p3, pos ? m1 : p2, pos ? c0 : p1, pos ? p1 : c0, pos ? p2 : m1);
+  if constexpr (DIV)
+    return u * weno_face_div(pos ? m2 : p3, pos ? m1 : p2, pos ? c0 : p1, pos ? p1 : c0, pos ? p2 : m1);
+  else
+    return u * weno_face(pos ? m2 : p3, pos ? m1 : p2, pos ? c0 : p1, pos ? p1 : c0, pos ? p2 : m1);
 }
 
 // Flux difference F(i+1/2) - F(i-1/2) at cell i from the seven values v[0..6] = cells i-3 ..
 // i+3 and the face velocities um (face i-1/2) and up (face i+1/2).
-template <typename T>
+template <bool DIV, typename T>
 __device__ __forceinline__ T weno_div1(const T v[7], T um, T up) {
-  const T fp = weno_flux(up, v[1], v[2], v[3], v[4], v[5], v[6]);
-  const T fm = weno_flux(um, v[0], v[1], v[2], v[3], v[4], v[5]);
+  const T fp = weno_flux<DIV>(up, v[1], v[2], v[3], v[4], v[5], v[6]);
+  const T fm = weno_flux<DIV>(um, v[0], v[1], v[2], v[3], v[4], v[5]);
   return fp - fm;
 }
 
@@ -85,6 +119,7 @@ struct WenoOffsets {
     }
   }
   // -(d(u q)/dx + d(v q)/dy + d(w q)/dz) of the array q at the cell, face velocities given
+  template <bool DIV>
   __device__ __forceinline__ T advection(const T* q, T um, T up, T vm, T vp, T wm, T wp, T ihx, T ihy,
                                          T ihz) const {
     T vx[7], vy[7], vz[7];
@@ -94,7 +129,7 @@ struct WenoOffsets {
       vy[d] = ld_at(q, y[d]);
       vz[d] = ld_at(q, z[d]);
     }
-    return -(weno_div1(vx, um, up) * ihx + weno_div1(vy, vm, vp) * ihy + weno_div1(vz, wm, wp) * ihz);
+    return -(weno_div1<DIV>(vx, um, up) * ihx + weno_div1<DIV>(vy, vm, vp) * ihy + weno_div1<DIV>(vz, wm, wp) * ihz);
   }
 };
 
