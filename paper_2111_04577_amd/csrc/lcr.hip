@@ -24,9 +24,27 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// Cyclic Jacobi for a symmetric 3x3 matrix: on exit a is diagonal (the eigenvalues) and the
-// columns of v are the eigenvectors. Stops when the off-diagonal mass is below 1e-32 of the
-// diagonal mass (relative 1e-16 per entry, FP64 round-off) or after 16 sweeps.
+// 1 / b and 1 / sqrt(x): the hardware estimates (about 2^-23 and 2^-24) refined once to third
+// order (error e -> e^3), without the scaling and special cases of the IEEE sequences: b and x
+// are normal and far from the ends of the range wherever they are used.
+__device__ __forceinline__ double recip3(double b) {
+  const double r = __builtin_amdgcn_rcp(b);
+  const double e = fma(-b, r, 1.0);
+  return fma(r * e, 1.0 + e, r);
+}
+__device__ __forceinline__ double rsqrt3(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// Cyclic Jacobi for a symmetric 3x3 matrix: on exit the diagonal of a holds the eigenvalues and
+// the columns of v are the eigenvectors. Stops when the off-diagonal mass is below 1e-32 of the
+// diagonal mass (relative 1e-16 per entry, FP64 round-off) or after 16 sweeps. Only the upper
+// triangle is kept up, and the tangent t of a rotation comes from one reciprocal square root
+// and one reciprocal (with d = (a_qq - a_pp) / 2: t = a_pq / (d + sgn(d) sqrt(d^2 + a_pq^2))),
+// its cosine from another: about 55 FP64 instructions a rotation, where the full matrix with
+// two IEEE divisions and two square roots took about 130.
 __device__ __forceinline__ void jacobi3(double a[3][3], double v[3][3]) {
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -35,30 +53,27 @@ __device__ __forceinline__ void jacobi3(double a[3][3], double v[3][3]) {
   for (int sweep = 0; sweep < 16; ++sweep) {
     const double off = a[0][1] * a[0][1] + a[0][2] * a[0][2] + a[1][2] * a[1][2];
     const double dia = a[0][0] * a[0][0] + a[1][1] * a[1][1] + a[2][2] * a[2][2];
-    if (off == 0.0 || off <= 1e-32 * dia) break;
+    if (off <= 1e-280 || off <= 1e-32 * dia) break;
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
-      const int p = r == 2 ? 1 : 0, q = r == 0 ? 1 : 2;
+      const int p = r == 2 ? 1 : 0, q = r == 0 ? 1 : 2, o = 3 - p - q;
       const double apq = a[p][q];
-      if (apq == 0.0) continue;
+      const double d = 0.5 * (a[q][q] - a[p][p]);
+      const double s2 = fma(d, d, apq * apq);
+      // entries below 1e-140 are zero here: their squares leave the range
+      if (apq == 0.0 || s2 < 1e-280) continue;
       // rotation that annihilates a[p][q] (the smaller of the two angles)
-      const double th = (a[q][q] - a[p][p]) / (2.0 * apq);
-      const double t = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-      const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
-      // a <- J^T a J with J the (p, q) rotation
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double akp = a[k][p], akq = a[k][q];
-        a[k][p] = c * akp - s * akq;
-        a[k][q] = s * akp + c * akq;
-      }
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double apk = a[p][k], aqk = a[q][k];
-        a[p][k] = c * apk - s * aqk;
-        a[q][k] = s * apk + c * aqk;
-      }
-      a[p][q] = a[q][p] = 0.0;
+      const double t = apq * recip3(d + copysign(s2 * rsqrt3(s2), d));
+      const double c = rsqrt3(fma(t, t, 1.0)), s = t * c;
+      // a <- J^T a J with J the (p, q) rotation, upper triangle (o: the third index)
+      a[p][p] = fma(-t, apq, a[p][p]);
+      a[q][q] = fma(t, apq, a[q][q]);
+      a[p][q] = 0.0;
+      double& aop = a[o < p ? o : p][o < p ? p : o];
+      double& aoq = a[o < q ? o : q][o < q ? q : o];
+      const double x = aop, y = aoq;
+      aop = c * x - s * y;
+      aoq = s * x + c * y;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         const double vkp = v[k][p], vkq = v[k][q];
@@ -69,12 +84,47 @@ __device__ __forceinline__ void jacobi3(double a[3][3], double v[3][3]) {
   }
 }
 
-// omega_ij (theta_j - theta_i) of eq. NS24 for d = theta_j - theta_i, without overflow:
-// (e^d m_ij + m_ji) d / expm1(d) for d < 0, (m_ij + e^{-d} m_ji) d / -expm1(-d) for d > 0.
+// e^x - 1 for x >= 0: x = k ln 2 + r, |r| <= ln 2 / 2, and 2^k expm1(r) + (2^k - 1) with the
+// Taylor polynomial of expm1 to r^14 (remainder 1e-17 relative). Infinite above 709.
+__device__ __forceinline__ double expm1_pos(double x) {
+  const double k = rint(x * 1.4426950408889634);
+  double r = fma(-k, 0.6931471805599453, x);
+  r = fma(-k, 2.3190468138462996e-17, r);
+  double p = 1.0 / 87178291200.0;
+  p = fma(p, r, 1.0 / 6227020800.0);
+  p = fma(p, r, 1.0 / 479001600.0);
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p * r, r, r);
+  const double two_k = ldexp(1.0, (int)k);
+  return x > 709.0 ? __builtin_huge_val() : fma(two_k, p, two_k - 1.0);
+}
+
+// e^x - 1 and e^-x - 1 from one evaluation: expm1(-|x|) = -P / (1 + P), P = expm1(|x|).
+__device__ __forceinline__ void expm1_pair(double x, double& ep, double& em) {
+  const double P = expm1_pos(fabs(x));
+  const double N = P > 1e300 ? -1.0 : -P * recip3(1.0 + P);
+  ep = x >= 0.0 ? P : N;
+  em = x >= 0.0 ? N : P;
+}
+
+// omega_ij (theta_j - theta_i) of eq. NS24 for d = theta_j - theta_i: (e^d m_ij + m_ji)
+// d / expm1(d), formed without overflow as (e^|d| m + m') |d| / expm1(|d|) with (m, m') = (m_ij,
+// m_ji) for d > 0 and swapped for d < 0; above |d| = 600 the ratio of the exponentials is 1.
 __device__ __forceinline__ double commutator_entry(double d, double mij, double mji) {
-  if (d == 0.0) return mij + mji;
-  if (d < 0.0) return (exp(d) * mij + mji) * (d / expm1(d));
-  return (mij + exp(-d) * mji) * (d / -expm1(-d));
+  const double x = fabs(d);
+  if (x == 0.0) return mij + mji;
+  const double m = d < 0.0 ? mji : mij, m1 = d < 0.0 ? mij : mji;
+  const double Q = expm1_pos(fmin(x, 600.0));
+  return fma(1.0 + Q, m, m1) * (x / Q);
 }
 
 // symmetric 3x3 <-> six components (xx, yy, zz, xy, xz, yz)
@@ -109,8 +159,12 @@ struct ThetaOut {
 // One stage: out = c0 Theta_n + c1 (Theta_in + dt RH(Theta_in)); LAST also writes tau_p from
 // the new Theta. Theta_n and out may be the same arrays (each thread reads Theta_n at its own
 // cell only; neighbours are read from Theta_in).
+//
+// Bound by arithmetic. FP32 is held to four waves per SIMD (128 VGPRs; the central last stage
+// spills 12 bytes): 128 x 128 x 64 cells, WENO-Z, the step 627 us at three waves, 600 at four,
+// 616 at five (116 bytes spilled); FP64 needs 148-162 VGPRs (three waves).
 template <typename T, bool LAST, bool WENO>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 3)))
     k_lcr_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w,
                 ThetaSet<T> thn, ThetaSet<T> thin, ThetaOut<T> thout, ThetaOut<T> tauout, int nx,
                 int ny, int nz, T ihx, T ihy, T ihz, double dt, double inv_wi, double alpha,
@@ -152,8 +206,9 @@ __global__ void __launch_bounds__(kBlock)
   double S[3][3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const double rel = -expm1(-th[a]) * (1.0 + alpha * expm1(th[a]));
-    S[a][a] = 2.0 * M[a][a] - inv_wi * rel;
+    double ep, em;
+    expm1_pair(th[a], ep, em);
+    S[a][a] = 2.0 * M[a][a] + inv_wi * (em * (1.0 + alpha * ep));
   }
   S[0][1] = S[1][0] = commutator_entry(th[1] - th[0], M[0][1], M[1][0]);
   S[0][2] = S[2][0] = commutator_entry(th[2] - th[0], M[0][2], M[2][0]);
@@ -217,7 +272,12 @@ __global__ void __launch_bounds__(kBlock)
     for (int a = 0; a < 3; ++a)
 #pragma unroll
       for (int b = 0; b < 3; ++b) Vq[a][b] = R[a][0] * Q[0][b] + R[a][1] * Q[1][b] + R[a][2] * Q[2][b];
-    const double e[3] = {expm1(B[0][0]), expm1(B[1][1]), expm1(B[2][2])};
+    double e[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      double em;
+      expm1_pair(B[a][a], e[a], em);
+    }
     double cm[6];
     rdr6(Vq, e, cm);
 #pragma unroll
