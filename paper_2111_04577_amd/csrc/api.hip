@@ -131,7 +131,7 @@ struct Carver {
 };
 
 struct TabOff {
-  size_t tw_xm, tw_xn, tw_y, lam_x, lam_y, ph_x, ph_y, tw_z, tw_zq, lam_z;
+  size_t tw_xm, tw_xn, tw_y, lam_x, lam_y, ph_x, ph_y, tw_z, tw_zq, lam_z, tw_zd, tw_zqd;
 };
 
 struct Offsets {
@@ -166,6 +166,12 @@ Offsets layout(const drpf_params& p, const Dims& F, const Dims& C) {
   for (int m = 0; m < 6; ++m) o.tau1[m] = p.viscoelastic ? cv.take(nc * es) : 0;
   o.part = cv.take(reduce_partials() * 8);
   o.obs = cv.take(8 * 8);
+  auto tabs64 = [&](const Dims& d, TabOff& t) {
+    t.tw_zd = es == 8 ? t.tw_z : cv.take((size_t)d.nz * 16);
+    t.tw_zqd = es == 8 ? t.tw_zq : cv.take((size_t)d.nz * 16);
+  };
+  tabs64(F, o.tf);
+  tabs64(C, o.tc);
   o.total = cv.off;
   return o;
 }
@@ -240,6 +246,8 @@ Tables<T> tables(drpf_grid* g, const TabOff& t) {
   tb.tw_z = reinterpret_cast<const cx<T>*>(g->ws + t.tw_z);
   tb.tw_zq = reinterpret_cast<const cx<T>*>(g->ws + t.tw_zq);
   tb.lam_z = reinterpret_cast<const double*>(g->ws + t.lam_z);
+  tb.tw_zd = reinterpret_cast<const cx<double>*>(g->ws + t.tw_zd);
+  tb.tw_zqd = reinterpret_cast<const cx<double>*>(g->ws + t.tw_zqd);
   return tb;
 }
 
@@ -320,6 +328,17 @@ int upload_tables(drpf_grid* g, const Dims& d, const TabOff& t, hipStream_t st,
     tw[2 * m + 1] = (T)-sinl(pi * m / (2 * d.nz));
   }
   HIPCHK(put(t.tw_zq, tw.data(), tw.size() * sizeof(T)), "upload twiddles");
+  if (sizeof(T) == 4) {
+    std::vector<double> td(2 * d.nz), tq(2 * d.nz);
+    for (int m = 0; m < d.nz; ++m) {
+      td[2 * m] = (double)cosl(2 * pi * m / d.nz);
+      td[2 * m + 1] = (double)-sinl(2 * pi * m / d.nz);
+      tq[2 * m] = (double)cosl(pi * m / (2 * d.nz));
+      tq[2 * m + 1] = (double)-sinl(pi * m / (2 * d.nz));
+    }
+    HIPCHK(put(t.tw_zd, td.data(), td.size() * 8), "upload twiddles");
+    HIPCHK(put(t.tw_zqd, tq.data(), tq.size() * 8), "upload twiddles");
+  }
   std::vector<double> lz(d.nz);
   for (int m = 0; m < d.nz; ++m) {
     const double s = sin(M_PI * m / (2.0 * d.nz));
@@ -607,26 +626,16 @@ int step_impl(drpf_grid* g, drpf_state* s, int nsteps, hipStream_t st) {
   return DRPF_OK;
 }
 
-// The solve's scratch: the spectral buffer S and the buffer R of the right-hand side with the
-// wall terms (used only with wall data); by default the grid's workspace buffers.
+// The solve's scratch: the spectral buffer S; by default the grid's workspace buffer.
 template <typename T>
 int helmholtz_impl(drpf_grid* g, int which, int bc, double coeff, double shift, const void* rhs,
-                   const void* wall, void* x, hipStream_t st, void* s_scr = nullptr,
-                   void* r_scr = nullptr) {
+                   const void* wall, void* x, hipStream_t st, void* s_scr = nullptr) {
   const Dims& d = which == DRPF_GRID_FINE ? g->F : g->C;
   const Tables<T> tb = tables<T>(g, which == DRPF_GRID_FINE ? g->o.tf : g->o.tc);
   cx<T>* S = s_scr ? reinterpret_cast<cx<T>*>(s_scr)
                    : reinterpret_cast<cx<T>*>(g->ws + (which == DRPF_GRID_FINE ? g->o.sf : g->o.sc));
-  const T* in[4] = {(const T*)rhs, nullptr, nullptr, nullptr};
-  if (wall) {
-    // the known wall terms move to the right-hand side: rhs - coeff b into the right-hand-side
-    // buffer, which the transforms then read
-    T* R = r_scr ? reinterpret_cast<T*>(r_scr)
-                 : reinterpret_cast<T*>(g->ws + (which == DRPF_GRID_FINE ? g->o.rf : g->o.rc));
-    HIPCHK(launch_wall_rhs<T>(d, bc, coeff, (const T*)rhs, (const T*)wall, R, st), "wall data");
-    in[0] = R;
-  }
-  HIPCHK(launch_fft_x_fwd<T>(d, tb, in, 1, S, st), "fft_x");
+  // the known wall terms move to the right-hand side as the x transform reads it
+  HIPCHK(launch_fft_x_fwd_wall<T>(d, tb, (const T*)rhs, (const T*)wall, bc, coeff, S, st), "fft_x");
   HIPCHK(launch_fft_y<T>(d, tb, S, 1, false, st), "fft_y");
   HIPCHK(launch_zpass_helmholtz<T>(d, tb, S, bc, coeff, shift, 1.0 / ((double)d.nx * d.ny), st),
          "zpass");
@@ -1151,8 +1160,8 @@ int drpf_helmholtz_solve_static(drpf_grid* g, int which_grid, int bc, double coe
   char* base = (char*)scr;
   hipStream_t st = (hipStream_t)stream;
   return g->p.precision == 64
-             ? helmholtz_impl<double>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, base, base + sbytes)
-             : helmholtz_impl<float>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, base, base + sbytes);
+             ? helmholtz_impl<double>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, base)
+             : helmholtz_impl<float>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, base);
 }
 
 int drpf_helmholtz_solve(drpf_grid* g, int which_grid, int bc, double coeff, double shift,

@@ -84,6 +84,8 @@ struct Tables {
   const cx<T>* tw_zq;    // e^{-i pi m / (2 nz)}, m < nz (DCT-II quarter-wave twiddle)
   const double* lam_z;   // -(4/hz^2) sin^2(pi m / (2 nz)), m < nz: DCT-II eigenvalues of the
                          // zero-flux second difference
+  const cx<double>* tw_zd;   // tw_z and tw_zq in FP64 (the same arrays on FP64 grids): the
+  const cx<double>* tw_zqd;  // standalone solve's wall-normal transform is FP64 on either grid
 };
 
 // Scheme constants of one step kind (first step: gamma0 = 1; later: 3/2).

@@ -21,16 +21,40 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// Wall data of a solve, read with the rows of its right-hand side: rows of the layers zb and zt
+// lose c times the row of the bottom or top wall layer.
+template <typename T>
+struct WallRows {
+  const T* w;  // bottom then top layer, Ny rows each
+  int zb, zt;
+  T c;
+  // the pair e (even, odd) of row r = z Ny + y, M pairs per row
+  __device__ __forceinline__ cx<T> apply(cx<T> v, int r, int k, int M, int Ny, int lny) const {
+    const int z = r >> lny, y = r & (Ny - 1);
+    if (z != zb && z != zt) return v;
+    const cx<T>* row = reinterpret_cast<const cx<T>*>(w);
+    if (z == zb) {
+      const cx<T> a = row[(size_t)y * M + k];
+      v = mk<T>(v.re - c * a.re, v.im - c * a.im);
+    }
+    if (z == zt) {
+      const cx<T> a = row[(size_t)(Ny + y) * M + k];
+      v = mk<T>(v.re - c * a.re, v.im - c * a.im);
+    }
+    return v;
+  }
+};
+
 // ---- x pass, forward (r2c) -------------------------------------------------------------
-// A block holds lpb rows (FftPlan line layout), T = M / P threads per row.
-template <typename T, int LOGM>
+// WALL: the rows next to the walls take the wall data of a solve. A block holds lpb rows (FftPlan line layout), T = M / P threads per row.
+template <typename T, int LOGM, bool WALL = false>
 __global__ void __launch_bounds__(kBlock) k_fft_x_fwd(const T* __restrict__ in0,
                                                       const T* __restrict__ in1,
                                                       const T* __restrict__ in2,
                                                       cx<T>* __restrict__ out,
                                                       int lines_per_field, int total_lines,
                                                       int lpb, int Ny, const cx<T>* __restrict__ twM,
-                                                      const cx<T>* __restrict__ twN) {
+                                                      const cx<T>* __restrict__ twN, WallRows<T> wr) {
   using F = FftPlan<LOGM, fft_lp<T>()>;
   constexpr int M = F::M;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -45,8 +69,11 @@ __global__ void __launch_bounds__(kBlock) k_fft_x_fwd(const T* __restrict__ in0,
   const T* src = in + (size_t)(line0 - field * lines_per_field) * (2 * M);
   // a row of 2M reals read as M (even, odd) pairs: rows start at even offsets of arrays
   // aligned to at least 16 bytes, so each pair is one aligned load
-  for (int e = threadIdx.x; e < nl * M; e += blockDim.x)
-    buf[(e >> LOGM) * F::LS + F::pad(e & (M - 1))] = reinterpret_cast<const cx<T>*>(src)[e];
+  for (int e = threadIdx.x; e < nl * M; e += blockDim.x) {
+    cx<T> v = reinterpret_cast<const cx<T>*>(src)[e];
+    if (WALL) v = wr.apply(v, line0 + (e >> LOGM), e & (M - 1), M, Ny, __ffs(Ny) - 1);
+    buf[(e >> LOGM) * F::LS + F::pad(e & (M - 1))] = v;
+  }
   __syncthreads();
   {
     const int b = threadIdx.x >> F::LT, q = threadIdx.x & (F::T - 1);
@@ -180,14 +207,14 @@ __global__ void __launch_bounds__(1024) k_fft_y(cx<T>* __restrict__ data, int P,
 // Every line is transformed by lds_fft (radix-4 Stockham, one butterfly set per thread).
 
 // ---- x pass, forward (r2c), run-time length ----------------------------------------------
-template <typename T>
+template <typename T, bool WALL = false>
 __global__ void __launch_bounds__(kBlock) k_fft_x_fwd_rt(const T* __restrict__ in0,
                                                       const T* __restrict__ in1,
                                                       const T* __restrict__ in2,
                                                       cx<T>* __restrict__ out, int N, int logM,
                                                       int lines_per_field, int total_lines,
                                                       int lpb, int Ny, const cx<T>* __restrict__ twM,
-                                                      const cx<T>* __restrict__ twN) {
+                                                      const cx<T>* __restrict__ twN, WallRows<T> wr) {
   extern __shared__ unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int M = N >> 1;
@@ -201,7 +228,11 @@ __global__ void __launch_bounds__(kBlock) k_fft_x_fwd_rt(const T* __restrict__ i
   const T* src = in + (size_t)(line0 - field * lines_per_field) * N;
   // a row of N reals read as N/2 (even, odd) pairs: rows start at even offsets of arrays
   // aligned to at least 16 bytes, so each pair is one aligned load
-  for (int e = threadIdx.x; e < nl * M; e += blockDim.x) buf[e] = reinterpret_cast<const cx<T>*>(src)[e];
+  for (int e = threadIdx.x; e < nl * M; e += blockDim.x) {
+    cx<T> v = reinterpret_cast<const cx<T>*>(src)[e];
+    if (WALL) v = wr.apply(v, line0 + (e >> logM), e & (M - 1), M, Ny, __ffs(Ny) - 1);
+    buf[e] = v;
+  }
   __syncthreads();
   lds_fft<T, false, false>(buf, M, logM, nl, 0, stw);
   // row r = z Ny + ky of this field
@@ -462,35 +493,52 @@ int x_lines_per_block(int M) {
 
 }  // namespace
 
-template <typename T>
-hipError_t launch_fft_x_fwd(const Dims& d, const Tables<T>& tb, const T* const in[4], int nfields,
-                            cx<T>* spec, hipStream_t st) {
+namespace {
+
+template <typename T, bool WALL>
+hipError_t fft_x_fwd_go(const Dims& d, const Tables<T>& tb, const T* const in[4], int nfields, cx<T>* spec,
+                        WallRows<T> wr, hipStream_t st) {
+  const T* i1 = nfields > 1 ? in[1] : in[0];
+  const T* i2 = nfields > 2 ? in[2] : in[0];
+  const int lpf = d.ny * d.nz;
+  const int total = lpf * nfields;
   if constexpr (sizeof(T) == 8) {
     const int M = d.nx / 2;
-    const int lpf = d.ny * d.nz;
     const int lpb = largest_pow2_divisor(lpf, x_lines_per_block(M));
-    const int total = lpf * nfields;
-    const int blocks = total / lpb;
     const size_t shm = (size_t)(lpb + 1) * M * sizeof(cx<T>);
-    hipLaunchKernelGGL(k_fft_x_fwd_rt<T>, dim3(blocks), dim3(kBlock), shm, st, in[0],
-                       nfields > 1 ? in[1] : in[0], nfields > 2 ? in[2] : in[0], spec, d.nx,
-                       d.logx - 1, lpf, total, lpb, d.ny, tb.tw_xm, tb.tw_xn);
+    hipLaunchKernelGGL((k_fft_x_fwd_rt<T, WALL>), dim3(total / lpb), dim3(kBlock), shm, st, in[0], i1, i2, spec,
+                       d.nx, d.logx - 1, lpf, total, lpb, d.ny, tb.tw_xm, tb.tw_xn, wr);
     return hipGetLastError();
   } else {
     const int logm = d.logx - 1;
-    const int lpf = d.ny * d.nz;
     const int lpb = x_lines_per_block16(logm, lpf);
-    const int total = lpf * nfields;
-    const int blocks = total / lpb;
     return with_logm(logm, [&](auto L) {
       constexpr int LOGM = decltype(L)::value;
       using F = FftPlan<LOGM, fft_lp<T>()>;
       const size_t shm = ((size_t)lpb * F::LS + F::M) * sizeof(cx<T>);
-      hipLaunchKernelGGL((k_fft_x_fwd<T, LOGM>), dim3(blocks), dim3(lpb * F::T), shm, st, in[0],
-                         nfields > 1 ? in[1] : in[0], nfields > 2 ? in[2] : in[0], spec, lpf, total, lpb,
-                         d.ny, tb.tw_xm, tb.tw_xn);
+      hipLaunchKernelGGL((k_fft_x_fwd<T, LOGM, WALL>), dim3(total / lpb), dim3(lpb * F::T), shm, st, in[0], i1, i2,
+                         spec, lpf, total, lpb, d.ny, tb.tw_xm, tb.tw_xn, wr);
     });
   }
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_fft_x_fwd(const Dims& d, const Tables<T>& tb, const T* const in[4], int nfields,
+                            cx<T>* spec, hipStream_t st) {
+  return fft_x_fwd_go<T, false>(d, tb, in, nfields, spec, WallRows<T>{}, st);
+}
+
+template <typename T>
+hipError_t launch_fft_x_fwd_wall(const Dims& d, const Tables<T>& tb, const T* in, const T* wall, int bc,
+                                 double coeff, cx<T>* spec, hipStream_t st) {
+  const T* set[4] = {in, nullptr, nullptr, nullptr};
+  if (!wall) return fft_x_fwd_go<T, false>(d, tb, set, 1, spec, WallRows<T>{}, st);
+  const double ihz = 1.0 / d.hz;
+  // coefficient of the wall value in b (both walls alike), times coeff
+  const double c = coeff * (bc == 0 ? ihz : bc == 1 ? 2.0 * ihz * ihz : ihz * ihz);
+  return fft_x_fwd_go<T, true>(d, tb, set, 1, spec, WallRows<T>{wall, 0, bc == 2 ? d.nz - 2 : d.nz - 1, (T)c}, st);
 }
 
 template <typename T>
@@ -621,6 +669,8 @@ hipError_t launch_fft_y(const Dims& d, const Tables<T>& tb, cx<T>* spec, int nfi
 #define INST(T)                                                                                    \
   template hipError_t launch_fft_x_fwd<T>(const Dims&, const Tables<T>&, const T* const[4], int,   \
                                           cx<T>*, hipStream_t);                                    \
+  template hipError_t launch_fft_x_fwd_wall<T>(const Dims&, const Tables<T>&, const T*, const T*, int, double, \
+                                               cx<T>*, hipStream_t);                               \
   template hipError_t launch_fft_x_inv<T>(const Dims&, const Tables<T>&, const cx<T>*, RealSet<T>, \
                                           hipStream_t);                                            \
   template hipError_t launch_fft_y<T>(const Dims&, const Tables<T>&, cx<T>*, int, bool, hipStream_t); \

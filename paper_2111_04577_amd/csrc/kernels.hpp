@@ -19,6 +19,13 @@ struct RealSet {
 template <typename T>
 hipError_t launch_fft_x_fwd(const Dims& d, const Tables<T>& tb, const T* const in[4], int nfields,
                             cx<T>* spec, hipStream_t st);
+// The forward x pass of one field whose right-hand side takes the wall data of a solve (wall, if
+// not null: the bottom then the top x-y layer): in - coeff b, b nonzero on the layers next to the
+// walls (bc 0: wall = outward normal derivative g, b = g / hz; bc 1: wall value, b = 2 wall /
+// hz^2; bc 2: wall value of the face field, b = wall / hz^2 on faces 0 and nz-2).
+template <typename T>
+hipError_t launch_fft_x_fwd_wall(const Dims& d, const Tables<T>& tb, const T* in, const T* wall, int bc,
+                                 double coeff, cx<T>* spec, hipStream_t st);
 template <typename T>
 hipError_t launch_fft_x_inv(const Dims& d, const Tables<T>& tb, const cx<T>* spec, RealSet<T> out,
                             hipStream_t st);
@@ -38,18 +45,10 @@ hipError_t launch_fft_xy_inv(const Dims& d, const Tables<T>& tb, const cx<T>* sp
 
 // ---- tridiag.hip ----------------------------------------------------------------------
 // bc: 0 Neumann, 1 Dirichlet (centred), 2 Dirichlet (z faces). Solves coeff L x - shift x =
-// (scale * spec) in place per Fourier mode; Neumann with shift 0 pins the zero mode and
-// removes its mean.
+// (scale * spec) in place per Fourier mode; Neumann with shift 0 drops the zero mode.
 template <typename T>
 hipError_t launch_zpass_helmholtz(const Dims& d, const Tables<T>& tb, cx<T>* spec, int bc,
                                   double coeff, double shift, double scale, hipStream_t st);
-// Wall data of a solve moved to its right-hand side: out = rhs - coeff b, b nonzero on the
-// layers next to the walls (bc 0: wall[] = outward normal derivative g, b = g / hz; bc 1: wall
-// value, b = 2 wall / hz^2; bc 2: wall value of the face field, b = wall / hz^2 on faces 0 and
-// nz-2, and layer nz-1 of out is 0). wall holds the bottom then the top x-y layer.
-template <typename T>
-hipError_t launch_wall_rhs(const Dims& d, int bc, double coeff, const T* rhs, const T* wall, T* out,
-                           hipStream_t st);
 // x[nz-1][.][.] = top (one x-y layer)
 template <typename T>
 hipError_t launch_top_layer(const Dims& d, const T* top, T* x, hipStream_t st);

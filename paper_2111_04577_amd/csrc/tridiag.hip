@@ -18,7 +18,7 @@
 //                velocity, the pressure-increment Poisson solve of eq. NS37 in FP64 with the
 //                (0,0) mode pinned and its mean removed, and the correction of eq. NS38
 //                (all per mode, in spectral x/y space).
-//   zpass_helmholtz -- one generic solve (the drpf_helmholtz_solve entry point).
+//   zpass_solve, zpass_helmholtz -- one generic solve (the drpf_helmholtz_solve entry point).
 #include "kernels.hpp"
 #include "lds_fft.hpp"
 #include "lds_fft16.hpp"
@@ -138,12 +138,12 @@ int spread_lines(int tl, int lines, int target, int per_line) {
   return tl;
 }
 
-// ---- generic Helmholtz (drpf_helmholtz_solve) ---------------------------------------
+// ---- generic Helmholtz (drpf_helmholtz_solve) with face-located walls -------------------
+// Unknowns on the z faces k = 0 .. nz-2, wall values 0; row nz-1 is an identity row.
 template <typename T>
 __global__ void __launch_bounds__(1024)
     k_zpass_helmholtz(cx<T>* __restrict__ S, int P, int Ny, int Nz, const double* __restrict__ lamx,
-                      const double* __restrict__ lamy, double ihz2, int bc, double coeff,
-                      double shift, double scale) {
+                      const double* __restrict__ lamy, double ihz2, double coeff, double shift, double scale) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int TL = blockDim.x / Nz;
   const int line = threadIdx.x % TL;
@@ -151,87 +151,89 @@ __global__ void __launch_bounds__(1024)
   const int lines = P * Ny;
   const int l = xcd_block() * TL + line;
   const bool valid = l < lines;
-  const int lc = valid ? l : lines - 1;
   int ky, kx;
-  spec_mode(lc, P, Ny, ky, kx);
+  spec_mode(valid ? l : lines - 1, P, Ny, ky, kx);
   const size_t stride = (size_t)lines;
   const double a = coeff * ihz2;
-  const double dxy = coeff * (lamx[kx] + lamy[ky]) - shift;
-  const bool pinned = bc == 0 && shift == 0.0 && kx == 0 && ky == 0;
-  const int n = bc == 2 ? Nz - 1 : Nz;
-  double ar = row == 0 ? 0.0 : a, cr = row == Nz - 1 ? 0.0 : a, br = dxy - 2 * a;
-  if (bc == 0) {
-    if (row == 0 || row == Nz - 1) br = dxy - a;
-  } else if (bc == 1) {
-    if (row == 0 || row == Nz - 1) br = dxy - 3 * a;
-  } else {
-    if (row == Nz - 2) cr = 0.0;
-    if (row == Nz - 1) { ar = 0.0; br = 1.0; }
-  }
-  cx<double> d[1];
-  d[0] = valid ? widen<double>(S[row * stride + l]) : mk<double>(0, 0);
-  d[0] = scale * d[0];
-  if (bc == 2 && row == Nz - 1) d[0] = mk<double>(0, 0);
-  // the singular (0,0) Neumann line: the pseudo-inverse drops the z-mean of the right-hand
-  // side first (the pinned row then reproduces the remaining equations exactly); every
-  // thread takes part in the barriers
-  {
-    cx<double>* Ls = reinterpret_cast<cx<double>*>(smem);
-    Ls[row * TL + line] = d[0];
-    __syncthreads();
-    if (pinned) {
-      double mre = 0, mim = 0;
-      for (int k = 0; k < Nz; ++k) {
-        mre += Ls[k * TL + line].re;
-        mim += Ls[k * TL + line].im;
-      }
-      d[0] = mk<double>(d[0].re - mre / Nz, d[0].im - mim / Nz);
-    }
-    __syncthreads();
-  }
-  if (pinned) {
-    if (row == 0) { ar = 0.0; cr = 0.0; br = 1.0; d[0] = mk<double>(0, 0); }
-    if (row == 1) ar = 0.0;
-  }
-  (void)n;
-  {
-    double a1[1] = {ar}, b1[1] = {br}, c1[1] = {cr};
-    pcr_sym<double, 1, 1, 0>(smem, Nz, TL, row, line, a1, b1, c1, d);
-  }
-  // zero-mean of the pinned mode: every thread takes part in the barrier
-  cx<double>* Ld = reinterpret_cast<cx<double>*>(smem);
-  Ld[row * TL + line] = d[0];
-  __syncthreads();
-  if (pinned) {
-    double mre = 0, mim = 0;
-    for (int k = 0; k < Nz; ++k) {
-      mre += Ld[k * TL + line].re;
-      mim += Ld[k * TL + line].im;
-    }
-    d[0] = mk<double>(d[0].re - mre / Nz, d[0].im - mim / Nz);
-  }
+  const bool top = row == Nz - 1;
+  double ar[1] = {row == 0 || top ? 0.0 : a}, cr[1] = {row >= Nz - 2 ? 0.0 : a};
+  double br[1] = {top ? 1.0 : coeff * (lamx[kx] + lamy[ky]) - shift - 2 * a};
+  cx<double> d[1] = {valid && !top ? scale * widen<double>(S[row * stride + l]) : mk<double>(0, 0)};
+  pcr_sym<double, 1, 1, 0>(smem, Nz, TL, row, line, ar, br, cr, d);
   if (valid) S[row * stride + l] = mk<T>((T)d[0].re, (T)d[0].im);
 }
 
-// ---- wall data of the generic solve moved to the right-hand side ----------------------
-template <typename T>
-__global__ void __launch_bounds__(256)
-    k_wall_rhs(const T* __restrict__ rhs, const T* __restrict__ wall, T* __restrict__ out, int layer,
-               int nz, int bc, T cb, T ct) {
-  const size_t n = (size_t)layer * nz;
-  for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < n; id += (size_t)gridDim.x * blockDim.x) {
-    const int k = (int)(id / layer);
-    const size_t e = id - (size_t)k * layer;
-    T r = rhs[id];
-    if (bc == 2) {
-      if (k == nz - 1) r = (T)0;
-      if (k == 0) r -= cb * wall[e];
-      if (k == nz - 2) r -= ct * wall[layer + e];
+// ---- generic solve by the wall-normal transform (Neumann and Dirichlet walls) ----------
+// coeff L x - shift x = rhs with zero-flux walls is diagonal in the DCT-II, with zero-value walls
+// (DIR) in the DST-II, which is the DCT-II of (-1)^k x_k with its coefficients reversed: the
+// same pass with the sign of every other row flipped on the way in and out and coefficient m
+// taking the eigenvalue of index nz - m. One LDS FFT each way (as in k_zpass_ch_rt) instead of
+// log2(nz) reduction steps with two barriers each over four FP64 planes per row; FP64 in both
+// storage types. A zero eigenvalue (Neumann, shift 0, kx = ky = m = 0) drops its coefficient: the
+// pseudo-inverse. 256 x 256 x 128, FP64: 82 us by reduction, 43 us so; the face-located walls
+// (bc 2) keep the reduction above.
+template <typename T, bool DIR>
+__global__ void __launch_bounds__(1024)
+    k_zpass_solve(cx<T>* __restrict__ S, int P, int Ny, int Nz, int logNz, int TL, const double* __restrict__ lamx,
+                  const double* __restrict__ lamy, const double* __restrict__ lamz, const cx<double>* __restrict__ twz,
+                  const cx<double>* __restrict__ twq, double coeff, double shift, double scale, double lam_top) {
+  using D = double;
+  extern __shared__ __align__(16) unsigned char smem[];
+  cx<D>* buf = reinterpret_cast<cx<D>*>(smem);  // [position][mode]
+  cx<D>* stw = buf + Nz * TL;                    // twiddles of the length-Nz transform
+  for (int e = threadIdx.x; e < Nz; e += blockDim.x) stw[e] = twz[e];
+  const int lines = P * Ny;
+  const int l0 = xcd_block() * TL;
+  const size_t stride = (size_t)lines;
+  const int ltl = __ffs(TL) - 1;  // TL is a power of two
+  for (int e = threadIdx.x; e < Nz * TL; e += blockDim.x) {
+    const int row = e >> ltl, t = e & (TL - 1);
+    const int l = l0 + t;
+    const int pos = (row & 1) ? (Nz - 1 - (row >> 1)) : (row >> 1);
+    const cx<D> v = l < lines ? widen<D>(S[row * stride + l]) : mk<D>(0, 0);
+    buf[(pos << ltl) + t] = DIR && (row & 1) ? mk<D>(-v.re, -v.im) : v;
+  }
+  __syncthreads();
+  lds_fft<D, false, true>(buf, Nz, logNz, TL, ltl, stw);
+  const int half = Nz >> 1;
+  auto dct_out = [&](cx<D> V, cx<D> Vp, cx<D> w) -> cx<D> {
+    const cx<D> A = 0.5 * (V + conj(Vp));
+    const cx<D> B = 0.5 * mul_mi(V - conj(Vp));
+    return mk<D>((w * A).re, (w * B).re);
+  };
+  for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
+    const int m = e >> ltl, t = e & (TL - 1);
+    const int l = min(l0 + t, lines - 1);
+    int ky, kx;
+    spec_mode(l, P, Ny, ky, kx);
+    const D lxy = lamx[kx] + lamy[ky];
+    const int mr = (Nz - m) & (Nz - 1);  // partner N - m (0 and N/2 pair with themselves)
+    auto gain = [&](int mm) -> D {
+      const D lz = DIR ? (mm == 0 ? lam_top : lamz[Nz - mm]) : lamz[mm];
+      const D den = coeff * (lxy + lz) - shift;
+      return den == 0.0 ? 0.0 : scale / den;
+    };
+    const cx<D> Vm = buf[(m << ltl) + t], Vr = buf[(mr << ltl) + t];
+    const cx<D> wm = twq[m];
+    const cx<D> Fm = gain(m) * dct_out(Vm, Vr, wm);
+    if (mr != m) {
+      const cx<D> wr = twq[mr];
+      const cx<D> Fr = gain(mr) * dct_out(Vr, Vm, wr);
+      buf[(m << ltl) + t] = conj(wm) * mk<D>(Fm.re + Fr.im, Fm.im - Fr.re);
+      buf[(mr << ltl) + t] = conj(wr) * mk<D>(Fr.re + Fm.im, Fr.im - Fm.re);
     } else {
-      if (k == 0) r -= cb * wall[e];
-      if (k == nz - 1) r -= ct * wall[layer + e];
+      buf[(m << ltl) + t] = m == 0 ? Fm : conj(wm) * mk<D>(Fm.re + Fm.im, Fm.im - Fm.re);
     }
-    out[id] = r;
+  }
+  __syncthreads();
+  lds_fft<D, true, true>(buf, Nz, logNz, TL, ltl, stw);
+  for (int e = threadIdx.x; e < Nz * TL; e += blockDim.x) {
+    const int row = e >> ltl, t = e & (TL - 1);
+    const int l = l0 + t;
+    const int pos = (row & 1) ? (Nz - 1 - (row >> 1)) : (row >> 1);
+    const cx<D> v = buf[(pos << ltl) + t];
+    const D sg = DIR && (row & 1) ? -1.0 : 1.0;
+    if (l < lines) S[row * stride + l] = mk<T>((T)(sg * v.re), (T)(sg * v.im));
   }
 }
 
@@ -801,24 +803,32 @@ template <typename T>
 hipError_t launch_zpass_helmholtz(const Dims& d, const Tables<T>& tb, cx<T>* spec, int bc,
                                   double coeff, double shift, double scale, hipStream_t st) {
   const int lines = d.lines();
+  if (bc != 2) {
+    // tiles of one cache line of modes, as in launch_zpass_ch
+    const int per_line = d.nz >= 4 ? d.nz / 4 : 1;
+    int TL = (int)(128 / sizeof(cx<T>));
+    while (TL > 1 && TL * d.nz > 4096) TL >>= 1;
+    TL = spread_lines(TL, lines, 2048, per_line);
+    const int threads = ((TL * per_line + 63) / 64) * 64;
+    int lognz = 0;
+    while ((1 << lognz) < d.nz) ++lognz;
+    const size_t shm = (size_t)d.nz * (TL + 1) * sizeof(cx<double>);
+    // the inverse transforms are unnormalised: fold 1/nz into the spectral scale
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((lines + TL - 1) / TL), dim3(threads), shm, st, spec, d.pitch, d.ny, d.nz, lognz,
+                         TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_zd, tb.tw_zqd, coeff, shift, scale / d.nz,
+                         -4.0 / (d.hz * d.hz));
+    };
+    if (bc == 1)
+      go(k_zpass_solve<T, true>);
+    else
+      go(k_zpass_solve<T, false>);
+    return hipGetLastError();
+  }
   const int TL = spread_lines(tile_lines(d.nz), lines, 2048, d.nz);
   const size_t shm = pcr_sym_bytes<double, 1, 1>(d.nz, TL);
   hipLaunchKernelGGL(k_zpass_helmholtz<T>, dim3((lines + TL - 1) / TL), dim3(TL * d.nz), shm, st, spec,
-                     d.pitch, d.ny, d.nz, tb.lam_x, tb.lam_y, 1.0 / (d.hz * d.hz), bc, coeff, shift,
-                     scale);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_wall_rhs(const Dims& d, int bc, double coeff, const T* rhs, const T* wall, T* out,
-                           hipStream_t st) {
-  const int layer = d.nx * d.ny;
-  const double ihz = 1.0 / d.hz;
-  // coefficient of the wall value in b (both walls alike), times coeff
-  const double c = coeff * (bc == 0 ? ihz : bc == 1 ? 2.0 * ihz * ihz : ihz * ihz);
-  const size_t n = (size_t)layer * d.nz;
-  const int blocks = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  hipLaunchKernelGGL(k_wall_rhs<T>, dim3(blocks), dim3(256), 0, st, rhs, wall, out, layer, d.nz, bc, (T)c, (T)c);
+                     d.pitch, d.ny, d.nz, tb.lam_x, tb.lam_y, 1.0 / (d.hz * d.hz), coeff, shift, scale);
   return hipGetLastError();
 }
 
@@ -939,8 +949,6 @@ hipError_t launch_zpass_ns_adj(const Dims& d, const Tables<double>& tb, cx<doubl
 #define INST(T)                                                                                  \
   template hipError_t launch_zpass_helmholtz<T>(const Dims&, const Tables<T>&, cx<T>*,  \
                                                 int, double, double, double, hipStream_t);       \
-  template hipError_t launch_wall_rhs<T>(const Dims&, int, double, const T*, const T*, T*,     \
-                                         hipStream_t);                                          \
   template hipError_t launch_top_layer<T>(const Dims&, const T*, T*, hipStream_t);             \
   template hipError_t launch_zpass_ch<T>(const Dims&, const Tables<T>&, cx<T>*, double, \
                                          double, double, double, hipStream_t, bool);             \
