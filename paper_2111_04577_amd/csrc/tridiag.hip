@@ -243,6 +243,90 @@ __global__ void __launch_bounds__(256)
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < layer; e += gridDim.x * blockDim.x) x[base + e] = top[e];
 }
 
+// Relaxed walls (eq. NS34 with D_w > 0): the operator is (L - c_psi)(L + alpha) + L dW, d = dwall
+// on the two wall-adjacent rows, a rank-two change of the Neumann product that the DCT
+// diagonalises. With F0 = X / A (A = (lambda - c_psi)(lambda + alpha), X the DCT of the
+// right-hand side, both scaled) the solution is F_m = F0_m - G_m s_m, G_m = d lambda_m c_m /
+// (N A_m), c_m = cos(pi m / 2N) = (row 0 of the DCT basis), s_m the sum (m even) or difference
+// (m odd) of the two wall values; since the inverse transform is x_k = sum_m W_m F_m cos(pi m
+// (k + 1/2) / N), W = (1, 2, 2, ...), the sum and difference solve sigma = P_e / (1 + H_e),
+// delta = P_o / (1 + H_o) with P = 2 sum W c F0 and H = 2 sum W c G over even or odd m. H >= 0
+// (d < 0, lambda <= 0, A > 0). Transposed (TRANS): the operator is (L - c_psi)(L + alpha) + dW L,
+// whose rank-two part takes the wall values of L x instead of x: G_m = d c_m / (N A_m), and P and
+// H weight each term by lambda_m (P = 2 sum W lambda c F0, H = 2 sum W lambda c G, the same H).
+//
+// Every thread keeps its coefficients F0 and G (at most NI pairs (m, N - m) of one mode t) in
+// registers from the sums to the correction; the sums (FP64) are reduced across the lanes of
+// each wavefront and then over the wavefronts through LDS (part: 6 TL doubles per wavefront), one
+// barrier in all. With F0, G and the partial sums in LDS and five barriers the pass took 73 us at
+// 256 x 256 x 128, FP64. coef(m, mr, t, ...) forms F0, lambda and 1 / A at m and mr = N - m from
+// the forward transform; store(m, mr, t, Fm, Fr) writes the inverse's input.
+template <typename T, bool TRANS, int NI, typename Coef, typename Store>
+__device__ __forceinline__ void relaxed_walls(int Nz, int TL, int ltl, const cx<T>* __restrict__ twq, T dwall,
+                                              double* part, Coef&& coef, Store&& store) {
+  const int half = Nz >> 1, t = threadIdx.x & (TL - 1), nth = blockDim.x;
+  const T dn = dwall / (T)Nz;
+  cx<T> Fm[NI], Fr[NI];
+  T Gm[NI], Gr[NI];
+  double acc[6] = {0, 0, 0, 0, 0, 0};  // P_e (re, im), P_o (re, im), H_e, H_o
+  auto add = [&](int m, T c, T lam, cx<T> F, T G) {
+    const double wc = (m == 0 ? 2.0 : 4.0) * (double)c * (TRANS ? (double)lam : 1.0);
+    const double fr = wc * (double)F.re, fi = wc * (double)F.im, g = wc * (double)G;
+    const bool odd = m & 1;
+    acc[0] += odd ? 0.0 : fr;
+    acc[1] += odd ? 0.0 : fi;
+    acc[2] += odd ? fr : 0.0;
+    acc[3] += odd ? fi : 0.0;
+    acc[4] += odd ? 0.0 : g;
+    acc[5] += odd ? g : 0.0;
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int e = threadIdx.x + i * nth;
+    if (e < (half + 1) * TL) {
+      const int m = e >> ltl, mr = (Nz - m) & (Nz - 1);
+      const cx<T> wm = twq[m], wr = twq[mr];
+      T lm, im, lr, ir;
+      coef(m, mr, t, wm, wr, Fm[i], Fr[i], lm, im, lr, ir);
+      Gm[i] = dn * (TRANS ? (T)1 : lm) * wm.re * im;
+      Gr[i] = dn * (TRANS ? (T)1 : lr) * wr.re * ir;
+      add(m, wm.re, lm, Fm[i], Gm[i]);
+      if (mr != m) add(mr, wr.re, lr, Fr[i], Gr[i]);
+    }
+  }
+  // lanes of one mode are TL apart; blocks have a power of two of threads, so every partner exists
+  const int wave = nth < 64 ? nth : 64, nw = nth < 64 ? 1 : nth >> 6;
+  for (int o = TL; o < wave; o <<= 1)
+#pragma unroll
+    for (int q = 0; q < 6; ++q) acc[q] += __shfl_xor(acc[q], o);
+  if (nw > 1) {
+    if ((int)(threadIdx.x & 63) < TL)
+#pragma unroll
+      for (int q = 0; q < 6; ++q) part[((threadIdx.x >> 6) * 6 + q) * TL + t] = acc[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 6; ++q) acc[q] = 0.0;
+    for (int w = 0; w < nw; ++w)
+#pragma unroll
+      for (int q = 0; q < 6; ++q) acc[q] += part[(w * 6 + q) * TL + t];
+  }
+  const double ie = 1.0 / (1.0 + acc[4]), io = 1.0 / (1.0 + acc[5]);
+  const cx<double> sigma = mk<double>(acc[0] * ie, acc[1] * ie), delta = mk<double>(acc[2] * io, acc[3] * io);
+  auto corrected = [&](int m, cx<T> F, T G) -> cx<T> {
+    const cx<double> s = (m & 1) ? delta : sigma;
+    return mk<T>((T)((double)F.re - (double)G * s.re), (T)((double)F.im - (double)G * s.im));
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int e = threadIdx.x + i * nth;
+    if (e < (half + 1) * TL) {
+      const int m = e >> ltl, mr = (Nz - m) & (Nz - 1);
+      const cx<T> a = corrected(m, Fm[i], Gm[i]);
+      store(m, mr, t, a, mr != m ? corrected(mr, Fr[i], Gr[i]) : a);
+    }
+  }
+}
+
 // ---- Cahn-Hilliard pair -------------------------------------------------------------
 // Both CH operators have zero-flux walls, so the DCT-II across the walls diagonalises them
 // exactly (eigenvalue lam_z(m) of the second difference for cos(pi m (k + 1/2) / nz)). The
@@ -322,86 +406,24 @@ __global__ void __launch_bounds__(kZBlock)
       inverse_in(m, mr, t, Fm, Fr);
     }
   } else {
-    // Relaxed walls (eq. NS34 with D_w > 0): the operator is (L - c_psi)(L + alpha) + L dW,
-    // d = dwall on the two wall-adjacent rows, a rank-two change of the Neumann product that
-    // the DCT diagonalises. With F0 = X / A (A = (lambda - c_psi)(lambda + alpha), X the DCT
-    // of the right-hand side, both scaled) the solution is F_m = F0_m - G_m s_m, G_m = d
-    // lambda_m c_m / (N A_m), c_m = cos(pi m / 2N) = (row 0 of the DCT basis), s_m the sum
-    // (m even) or difference (m odd) of the two wall values; since the inverse transform is
-    // x_k = sum_m W_m F_m cos(pi m (k + 1/2) / N), W = (1, 2, 2, ...), the sum and difference
-    // solve sigma = P_e / (1 + H_e), delta = P_o / (1 + H_o) with P = 2 sum W c F0 and
-    // H = 2 sum W c G over even or odd m. H >= 0 (d < 0, lambda <= 0, A > 0).
-    // after the twiddles, rounded up to 16 bytes: the wall sums [TL][2], the partials
-    // [NC][TL][6], then G [Nz][TL] in the storage type
-    const int NC = min((int)(blockDim.x >> ltl), 16);
+    // a thread's entries all belong to one mode (blockDim is a multiple of TL)
+    int ky, kx;
+    spec_mode(min(l0 + (int)(threadIdx.x & (TL - 1)), lines - 1), P, Ny, ky, kx);
+    const T lxy = (T)(lamx[kx] + lamy[ky]);
+    // after the twiddles, rounded up to 16 bytes: the wavefronts' partial sums
     const size_t so = ((size_t)(TL * F::LS + Nz) * sizeof(cx<T>) + 15) & ~(size_t)15;
-    cx<double>* sd = reinterpret_cast<cx<double>*>(smem + so);
-    double* part = reinterpret_cast<double*>(sd + 2 * TL);
-    T* sG = reinterpret_cast<T*>(part + 6 * NC * TL);
-    for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
-      const int m = e >> ltl, t = e & (TL - 1);
-      const int l = min(l0 + t, lines - 1);
-      int ky, kx;
-      spec_mode(l, P, Ny, ky, kx);
-      const T lxy = (T)(lamx[kx] + lamy[ky]);
-      const int mr = (Nz - m) & (Nz - 1);
-      const cx<T> Vm = at(m, t), Vr = at(mr, t);
-      // 1/A once per entry: F0 = scale X / A and G = d lambda c / (N A)
-      const T lm = lxy + (T)lamz[m];
-      const T im = recip((lm - cp) * (lm + al));
-      at(m, t) = (sc * im) * dct_out(Vm, Vr, twq[m]);
-      sG[m * TL + t] = (T)dwall * lm * twq[m].re * im / (T)Nz;
-      if (mr != m) {
-        const T lr = lxy + (T)lamz[mr];
-        const T ir = recip((lr - cp) * (lr + al));
-        at(mr, t) = (sc * ir) * dct_out(Vr, Vm, twq[mr]);
-        sG[mr * TL + t] = (T)dwall * lr * twq[mr].re * ir / (T)Nz;
-      }
-    }
-    __syncthreads();
-    // partial sums over m = ch, ch + NC, ... per mode, then their totals
-    for (int e = threadIdx.x; e < NC * TL; e += blockDim.x) {
-      const int t = e & (TL - 1), ch = e >> ltl;
-      double acc[6] = {0, 0, 0, 0, 0, 0};  // P_e (re, im), P_o (re, im), H_e, H_o
-      for (int m = ch; m < Nz; m += NC) {
-        const double wc = (m == 0 ? 2.0 : 4.0) * (double)twq[m].re;
-        const cx<T> Fv = at(m, t);
-        const int o = (m & 1) * 2;
-        acc[o] += wc * (double)Fv.re;
-        acc[o + 1] += wc * (double)Fv.im;
-        acc[4 + (m & 1)] += wc * (double)sG[m * TL + t];
-      }
-#pragma unroll
-      for (int q = 0; q < 6; ++q) part[(ch * TL + t) * 6 + q] = acc[q];
-    }
-    __syncthreads();
-    // totals: one thread per (quantity, mode), into the first chunk's slots
-    for (int e = threadIdx.x; e < 6 * TL; e += blockDim.x) {
-      const int t = e % TL, q = e / TL;
-      double a = 0;
-      for (int ch = 0; ch < NC; ++ch) a += part[(ch * TL + t) * 6 + q];
-      part[t * 6 + q] = a;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < TL; t += blockDim.x) {
-      const double* a = part + t * 6;
-      sd[2 * t] = mk<double>(a[0] / (1.0 + a[4]), a[1] / (1.0 + a[4]));      // sigma
-      sd[2 * t + 1] = mk<double>(a[2] / (1.0 + a[5]), a[3] / (1.0 + a[5]));  // delta
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
-      const int m = e >> ltl, t = e & (TL - 1);
-      const int mr = (Nz - m) & (Nz - 1);
-      auto corrected = [&](int mm) -> cx<T> {
-        const cx<T> Fv = at(mm, t);
-        const cx<double> s = sd[2 * t + (mm & 1)];
-        const double g = (double)sG[mm * TL + t];
-        return mk<T>((T)((double)Fv.re - g * s.re), (T)((double)Fv.im - g * s.im));
-      };
-      const cx<T> Fm = corrected(m);
-      const cx<T> Fr = mr != m ? corrected(mr) : Fm;
-      inverse_in(m, mr, t, Fm, Fr);
-    }
+    relaxed_walls<T, false, 5>(
+        Nz, TL, ltl, twq, (T)dwall, reinterpret_cast<double*>(smem + so),
+        [&](int m, int mr, int t, cx<T> wm, cx<T> wr, cx<T>& Fm, cx<T>& Fr, T& lm, T& im, T& lr, T& ir) {
+          const cx<T> Vm = at(m, t), Vr = at(mr, t);
+          lm = lxy + (T)lamz[m];
+          im = recip((lm - cp) * (lm + al));
+          Fm = (sc * im) * dct_out(Vm, Vr, wm);
+          lr = lxy + (T)lamz[mr];
+          ir = recip((lr - cp) * (lr + al));
+          Fr = (sc * ir) * dct_out(Vr, Vm, wr);
+        },
+        inverse_in);
   }
   __syncthreads();
   fft16<T, true, LOGNZ, fft_lp<T>()>(buf + fb * F::LS, fq, fb < TL, stw);
@@ -479,95 +501,24 @@ __global__ void __launch_bounds__(1024)
       inverse_in(m, mr, t, Fm, Fr);
     }
   } else {
-    // Relaxed walls (eq. NS34 with D_w > 0): the operator is (L - c_psi)(L + alpha) + L dW,
-    // d = dwall on the two wall-adjacent rows, a rank-two change of the Neumann product that
-    // the DCT diagonalises. With F0 = X / A (A = (lambda - c_psi)(lambda + alpha), X the DCT
-    // of the right-hand side, both scaled) the solution is F_m = F0_m - G_m s_m, G_m = d
-    // lambda_m c_m / (N A_m), c_m = cos(pi m / 2N) = (row 0 of the DCT basis), s_m the sum
-    // (m even) or difference (m odd) of the two wall values; since the inverse transform is
-    // x_k = sum_m W_m F_m cos(pi m (k + 1/2) / N), W = (1, 2, 2, ...), the sum and difference
-    // solve sigma = P_e / (1 + H_e), delta = P_o / (1 + H_o) with P = 2 sum W c F0 and
-    // H = 2 sum W c G over even or odd m. H >= 0 (d < 0, lambda <= 0, A > 0).
-    // Transposed (TRANS): the operator is (L - c_psi)(L + alpha) + dW L, whose rank-two part
-    // takes the wall values of L x instead of x: G_m = d c_m / (N A_m), and P and H weight each
-    // term by lambda_m (P = 2 sum W lambda c F0, H = 2 sum W lambda c G, the same H as above).
-    // after the twiddles, rounded up to 16 bytes: the wall sums [TL][2], the partials
-    // [NC][TL][6], then G [Nz][TL] in the storage type
-    const int NC = min((int)(blockDim.x >> ltl), 16);
+    // a thread's entries all belong to one mode (blockDim is a multiple of TL)
+    int ky, kx;
+    spec_mode(min(l0 + (int)(threadIdx.x & (TL - 1)), lines - 1), P, Ny, ky, kx);
+    const T lxy = (T)(lamx[kx] + lamy[ky]);
+    // after the twiddles, rounded up to 16 bytes: the wavefronts' partial sums
     const size_t so = ((size_t)(Nz * TL + Nz) * sizeof(cx<T>) + 15) & ~(size_t)15;
-    cx<double>* sd = reinterpret_cast<cx<double>*>(smem + so);
-    double* part = reinterpret_cast<double*>(sd + 2 * TL);
-    T* sG = reinterpret_cast<T*>(part + 6 * NC * TL);
-    for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
-      const int m = e >> ltl, t = e & (TL - 1);
-      const int l = min(l0 + t, lines - 1);
-      int ky, kx;
-      spec_mode(l, P, Ny, ky, kx);
-      const T lxy = (T)(lamx[kx] + lamy[ky]);
-      const int mr = (Nz - m) & (Nz - 1);
-      const cx<T> Vm = buf[m * TL + t], Vr = buf[mr * TL + t];
-      // 1/A once per entry: F0 = scale X / A and G = d lambda c / (N A)
-      const T lm = lxy + (T)lamz[m];
-      const T im = recip((lm - cp) * (lm + al));
-      buf[m * TL + t] = (sc * im) * dct_out(Vm, Vr, twq[m]);
-      sG[m * TL + t] = (T)dwall * (TRANS ? (T)1 : lm) * twq[m].re * im / (T)Nz;
-      if (mr != m) {
-        const T lr = lxy + (T)lamz[mr];
-        const T ir = recip((lr - cp) * (lr + al));
-        buf[mr * TL + t] = (sc * ir) * dct_out(Vr, Vm, twq[mr]);
-        sG[mr * TL + t] = (T)dwall * (TRANS ? (T)1 : lr) * twq[mr].re * ir / (T)Nz;
-      }
-    }
-    __syncthreads();
-    // partial sums over m = ch, ch + NC, ... per mode, then their totals
-    for (int e = threadIdx.x; e < NC * TL; e += blockDim.x) {
-      const int t = e & (TL - 1), ch = e >> ltl;
-      T lxy = (T)0;
-      if (TRANS) {
-        int ky, kx;
-        spec_mode(min(l0 + t, lines - 1), P, Ny, ky, kx);
-        lxy = (T)(lamx[kx] + lamy[ky]);
-      }
-      double acc[6] = {0, 0, 0, 0, 0, 0};  // P_e (re, im), P_o (re, im), H_e, H_o
-      for (int m = ch; m < Nz; m += NC) {
-        const double wc = (m == 0 ? 2.0 : 4.0) * (double)twq[m].re * (TRANS ? (double)(lxy + (T)lamz[m]) : 1.0);
-        const cx<T> F = buf[m * TL + t];
-        const int o = (m & 1) * 2;
-        acc[o] += wc * (double)F.re;
-        acc[o + 1] += wc * (double)F.im;
-        acc[4 + (m & 1)] += wc * (double)sG[m * TL + t];
-      }
-#pragma unroll
-      for (int q = 0; q < 6; ++q) part[(ch * TL + t) * 6 + q] = acc[q];
-    }
-    __syncthreads();
-    // totals: one thread per (quantity, mode), into the first chunk's slots
-    for (int e = threadIdx.x; e < 6 * TL; e += blockDim.x) {
-      const int t = e % TL, q = e / TL;
-      double a = 0;
-      for (int ch = 0; ch < NC; ++ch) a += part[(ch * TL + t) * 6 + q];
-      part[t * 6 + q] = a;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < TL; t += blockDim.x) {
-      const double* a = part + t * 6;
-      sd[2 * t] = mk<double>(a[0] / (1.0 + a[4]), a[1] / (1.0 + a[4]));      // sigma
-      sd[2 * t + 1] = mk<double>(a[2] / (1.0 + a[5]), a[3] / (1.0 + a[5]));  // delta
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
-      const int m = e >> ltl, t = e & (TL - 1);
-      const int mr = (Nz - m) & (Nz - 1);
-      auto corrected = [&](int mm) -> cx<T> {
-        const cx<T> F = buf[mm * TL + t];
-        const cx<double> s = sd[2 * t + (mm & 1)];
-        const double g = (double)sG[mm * TL + t];
-        return mk<T>((T)((double)F.re - g * s.re), (T)((double)F.im - g * s.im));
-      };
-      const cx<T> Fm = corrected(m);
-      const cx<T> Fr = mr != m ? corrected(mr) : Fm;
-      inverse_in(m, mr, t, Fm, Fr);
-    }
+    relaxed_walls<T, TRANS, 3>(
+        Nz, TL, ltl, twq, (T)dwall, reinterpret_cast<double*>(smem + so),
+        [&](int m, int mr, int t, cx<T> wm, cx<T> wr, cx<T>& Fm, cx<T>& Fr, T& lm, T& im, T& lr, T& ir) {
+          const cx<T> Vm = buf[m * TL + t], Vr = buf[mr * TL + t];
+          lm = lxy + (T)lamz[m];
+          im = recip((lm - cp) * (lm + al));
+          Fm = (sc * im) * dct_out(Vm, Vr, wm);
+          lr = lxy + (T)lamz[mr];
+          ir = recip((lr - cp) * (lr + al));
+          Fr = (sc * ir) * dct_out(Vr, Vm, wr);
+        },
+        inverse_in);
   }
   __syncthreads();
   lds_fft<T, true, true>(buf, Nz, logNz, TL, ltl, stw);
@@ -862,10 +813,8 @@ hipError_t launch_zpass_ch(const Dims& d, const Tables<T>& tb, cx<T>* spec, doub
                          d.pitch, d.ny, d.nz, lognz, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi,
                          alpha, scale / d.nz, 0.0);
     } else {
-      // relaxed walls: partial sums (at most 16 per mode, 6 doubles each) and the wall sums
-      const int nc = (threads / TL) < 16 ? threads / TL : 16;
-      shm = ((shm + 15) & ~(size_t)15) + (size_t)2 * TL * sizeof(cx<double>) + (size_t)6 * nc * TL * sizeof(double) +
-            (size_t)d.nz * TL * sizeof(T);
+      // relaxed walls: 6 partial sums per mode and wavefront
+      shm = ((shm + 15) & ~(size_t)15) + (size_t)6 * (threads / 64) * TL * sizeof(double);
       auto kern = trans ? k_zpass_ch_rt<T, true, true> : k_zpass_ch_rt<T, true, false>;
       hipLaunchKernelGGL(kern, dim3((lines + TL - 1) / TL), dim3(threads), shm, st, spec, d.pitch, d.ny, d.nz,
                          lognz, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi, alpha, scale / d.nz,
@@ -893,10 +842,8 @@ hipError_t launch_zpass_ch(const Dims& d, const Tables<T>& tb, cx<T>* spec, doub
                            spec, d.pitch, d.ny, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi, alpha,
                            scale / d.nz, 0.0);
       } else {
-        // relaxed walls: partial sums (at most 16 per mode, 6 doubles each) and the wall sums
-        const int nc = (threads / TL) < 16 ? threads / TL : 16;
-        shm = ((shm + 15) & ~(size_t)15) + (size_t)2 * TL * sizeof(cx<double>) + (size_t)6 * nc * TL * sizeof(double) +
-              (size_t)d.nz * TL * sizeof(T);
+        // relaxed walls: 6 partial sums per mode and wavefront
+        shm = ((shm + 15) & ~(size_t)15) + (size_t)6 * ((threads + 63) / 64) * TL * sizeof(double);
         hipLaunchKernelGGL((k_zpass_ch<T, true, LOGNZ>), dim3((lines + TL - 1) / TL), dim3(threads), shm, st,
                            spec, d.pitch, d.ny, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi, alpha,
                            scale / d.nz, dwall);
