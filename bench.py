@@ -97,6 +97,8 @@ def alg_bytes(kernel, cfg, es):
         # with WENO-Z the advection arrives precomputed (read once) instead of the velocities
         "ch_rhs": 4 * nf if cfg.advection == 1 else 3 * nf + 6 * nc,
         "weno_adv_fine": 3 * nf + 6 * nc if cfg.advection == 1 else 0,
+        # the right-hand side transformed in the pass that forms it: neither written nor read
+        "ch_rhs_fft_x": (3 * nf if cfg.advection == 1 else 2 * nf + 6 * nc) + sf,
         "fft_x_fwd_fine": nf + sf,
         "fft_y_fwd_fine": 2 * sf if F["ny"] > 1 else 0,
         "zpass_ch": 2 * sf,
@@ -124,7 +126,7 @@ def alg_bytes(kernel, cfg, es):
 
 
 KERNEL_SOURCE = {
-    "ch_rhs": "stencil_ch.hip", "restrict_g": "stencil_ch.hip", "weno_adv_fine": "stencil_ch.hip",
+    "ch_rhs": "stencil_ch.hip", "ch_rhs_fft_x": "ch_fft.hip", "restrict_g": "stencil_ch.hip", "weno_adv_fine": "stencil_ch.hip",
     "momentum_rhs": "stencil_ns.hip",
     "polymer_stage1": "stencil_ns.hip", "polymer_stage2": "stencil_ns.hip", "polymer_rk2": "stencil_ns.hip",
     "zpass_ch": "tridiag.hip", "zpass_ns": "tridiag.hip",
@@ -473,7 +475,7 @@ def ingest_pmc(fetch_csv, write_csv, out_json, workload):
     write, ws = read(write_csv, "WRITE_SIZE")
     # the polymer divergence pass is timed with the momentum kernel (one profiling id): its bytes
     # are added to momentum_rhs's
-    base = {"k_ch_rhs": "ch_rhs", "k_restrict_g": "restrict_g", "k_momentum_rhs": "momentum_rhs",
+    base = {"k_ch_rhs": "ch_rhs", "k_ch_fft": "ch_rhs_fft_x", "k_restrict_g": "restrict_g", "k_momentum_rhs": "momentum_rhs",
             "k_momentum_rhs_zm": "momentum_rhs", "k_polymer_div_zm": "momentum_rhs", "k_polymer_rk2_zm": "polymer_rk2",
             "k_zpass_ch": "zpass_ch", "k_zpass_ns": "zpass_ns",
             "k_fft_xy_fwd": "fft_xy_fwd_coarse", "k_fft_xy_inv": "fft_xy_inv_coarse"}
@@ -492,7 +494,9 @@ def ingest_pmc(fetch_csv, write_csv, out_json, workload):
         if k in base:
             name = base[k]
         elif k in ("k_fft_x_fwd", "k_fft_x_inv", "k_fft_y"):
-            grid = "fine" if g == max(sizes[(k, t, inv)]) else "coarse"
+            # with the right-hand side transformed in its own pass only coarse rows are left here
+            fused = k == "k_fft_x_fwd" and any(o[0] == "k_ch_fft" and o[1] == t for o in fetch)
+            grid = "fine" if g == max(sizes[(k, t, inv)]) and not fused else "coarse"
             kind = {"k_fft_x_fwd": "fft_x_fwd", "k_fft_x_inv": "fft_x_inv"}.get(k)
             if kind is None:
                 kind = "fft_y_inv" if inv == "true" else "fft_y_fwd"

@@ -302,8 +302,10 @@ int drpf_debug_field(drpf_grid* g, int id, void** ptr, size_t* count);
  * advection of the phase field (advection 1 only; it precedes ch_rhs), 16-17 the coarse x and
  * y transforms in one kernel, forward and inverse (in place of 8-9 and 11-12 where a coarse
  * layer fits in one block's LDS: 128 x 128 in either precision), 18 both polymer stages in one
- * pass (in place of 13-14 for 3D grids with central advection and the stress form). */
-#define DRPF_NKERNELS 19
+ * pass (in place of 13-14 for 3D grids with central advection and the stress form), 19 the
+ * right-hand side and its x transform in one pass (in place of 0 and 1 where a block holds whole
+ * rows: phase-field rows of 16 to 1024 points, in 3D FP64 to 512, but for moving relaxed walls). */
+#define DRPF_NKERNELS 20
 int drpf_profile_begin(drpf_grid* g, int max_launches, void* stream);
 int drpf_profile_end(drpf_grid* g, double* total_ms, int* launches, int n);
 /* Short name of kernel id (see above); "" for an unknown id. */

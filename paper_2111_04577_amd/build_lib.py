@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdrpf.so")
-SOURCES = ["api.hip", "fft.hip", "tridiag.hip", "stencil_ch.hip", "stencil_ns.hip", "reduce.hip",
+SOURCES = ["api.hip", "fft.hip", "tridiag.hip", "stencil_ch.hip", "ch_fft.hip", "stencil_ns.hip", "reduce.hip",
            "adjoint.hip", "lcr.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -352,7 +352,7 @@ const char* const kKernelNames[DRPF_NKERNELS] = {
     "ch_rhs", "fft_x_fwd_fine", "fft_y_fwd_fine", "zpass_ch", "fft_y_inv_fine", "fft_x_inv_fine",
     "restrict_g", "momentum_rhs", "fft_x_fwd_coarse", "fft_y_fwd_coarse", "zpass_ns",
     "fft_y_inv_coarse", "fft_x_inv_coarse", "polymer_stage1", "polymer_stage2", "weno_adv_fine",
-    "fft_xy_fwd_coarse", "fft_xy_inv_coarse", "polymer_rk2"};
+    "fft_xy_fwd_coarse", "fft_xy_inv_coarse", "polymer_rk2", "ch_rhs_fft_x"};
 
 void mark(drpf_grid* g, int kernel, hipStream_t st) {
   if (!g->prof || g->ev_used >= g->ev.size()) return;
@@ -394,17 +394,23 @@ int step_one(drpf_grid* g, const StepIO<T>& io, const StepConsts& K, hipStream_t
   // ---- Cahn-Hilliard on the fine grid
   ChIn<T> ci{io.phin, io.phinm1, io.un, io.unm1, io.vn, io.vnm1, io.wn, io.wnm1, nullptr};
   if (g->p.advection == 1) {
-    // WENO-Z advection first, into the fine spectral buffer (free until the transform)
-    T* adv = reinterpret_cast<T*>(Sf);
+    // WENO-Z advection first, into the right-hand side's buffer (the fused pass writes the
+    // spectral buffer), else into the fine spectral buffer (free until the transform)
+    T* adv = ch_fft_fits<T>(F, K) ? Rf : reinterpret_cast<T*>(Sf);
     HIPCHK(launch_weno_adv_fine<T>(F, C, K, ci, adv, st), "weno advection");
     mark(g, 15, st);
     ci.adv = adv;
   }
-  HIPCHK(launch_ch_rhs<T>(F, C, K, ci, Rf, st), "ch_rhs");
-  mark(g, 0, st);
-  const T* inf[4] = {Rf, nullptr, nullptr, nullptr};
-  HIPCHK(launch_fft_x_fwd<T>(F, tf, inf, 1, Sf, st), "fft_x fine");
-  mark(g, 1, st);
+  if (ch_fft_fits<T>(F, K)) {
+    HIPCHK(launch_ch_fft<T>(F, C, K, tf, ci, Sf, st), "ch_rhs and fft_x fine");
+    mark(g, 19, st);
+  } else {
+    HIPCHK(launch_ch_rhs<T>(F, C, K, ci, Rf, st), "ch_rhs");
+    mark(g, 0, st);
+    const T* inf[4] = {Rf, nullptr, nullptr, nullptr};
+    HIPCHK(launch_fft_x_fwd<T>(F, tf, inf, 1, Sf, st), "fft_x fine");
+    mark(g, 1, st);
+  }
   HIPCHK(launch_fft_y<T>(F, tf, Sf, 1, false, st), "fft_y fine");
   mark(g, 2, st);
   HIPCHK(launch_zpass_ch<T>(F, tf, Sf, K.c_psi, K.alpha, 1.0 / ((double)F.nx * F.ny),

@@ -80,6 +80,14 @@ template <typename T>
 hipError_t launch_ch_rhs(const Dims& f, const Dims& c, const StepConsts& k, ChIn<T> in, T* rhs,
                          hipStream_t st);
 
+// The right-hand side and its forward x transform in one pass (ch_fft.hip); ch_fft_fits says
+// whether the grid and walls take it.
+template <typename T>
+bool ch_fft_fits(const Dims& f, const StepConsts& k);
+template <typename T>
+hipError_t launch_ch_fft(const Dims& f, const Dims& c, const StepConsts& k, const Tables<T>& tb, ChIn<T> in,
+                         cx<T>* spec, hipStream_t st);
+
 // Restricted coarse set written by launch_restrict_g.
 template <typename T>
 struct Restricted {
