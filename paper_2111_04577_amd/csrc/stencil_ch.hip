@@ -36,16 +36,10 @@ constexpr int kBlock = 256;
 // the column enters a new coarse layer. The 3D FP32 form is held to 64 registers, so that the
 // 8 blocks per CU of a 256 x 256 x 128 grid are resident at once. SR: single resolution (the
 // phase field on the flow grid; the face velocities are taken as they are).
-//
-// RELAX (eq. NS34 with D_w > 0, walls at rest): the wall data b, with phi_hat of the wall-adjacent
-// layer in them, are formed once for the tile when a wall layer enters the ring, from the values
-// at hand there, into an LDS tile per wall; read from memory at the five points of every cell of a
-// wall layer they cost the march its registers (FP64, 256 x 256 x 128: 130 us at three waves per
-// SIMD against 83 us for static walls).
 template <typename T, int R, int MODE, bool RELAX, int TXC = 0, bool MOVE = false>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && R == 2 && MODE == 0 && !RELAX ? 8
-                                       : (MOVE && sizeof(T) == 8 ? 3 : 4))))
+                                       : (RELAX && sizeof(T) == 8 ? 3 : 4))))
     k_ch_rhs(const T* __restrict__ phin, const T* __restrict__ phinm1, Prolonged<T> pv,
              T* __restrict__ out, const T* __restrict__ advp, int nx, int ny, int nz, int KB, T ihx,
              T ihy, T ihz, StepConsts c) {
@@ -58,8 +52,6 @@ __global__ void __launch_bounds__(kBlock)
   const int HX = TX + 2, HY = TY + 2, HP = HX * HY;
   T* sP = reinterpret_cast<T*>(smem);  // 3 slots of phi*
   T* sW = sP + 3 * HP;                 // 3 slots of w* = f(phi*) - (S/Cn^2) phi*
-  constexpr bool BT = RELAX && !MOVE;  // wall data b of the bottom and the top layer in LDS
-  T* sB = sW + 3 * HP;
   const int tx = threadIdx.x, ty = threadIdx.y;
   const int tid = ty * TX + tx, nth = TX * TY;
   const int I = X0 + tx, J = Y0 + ty;
@@ -90,20 +82,13 @@ __global__ void __launch_bounds__(kBlock)
       }
     }
   };
-  constexpr bool relax = RELAX;  // relaxed walls (eq. NS34 with D_w > 0)
-  const T gb = (T)c.g_bot * ihz, gt = (T)c.g_top * ihz;
-  const T kg = RELAX ? (T)(c.relax_kappa * c.inv_gamma0) * ihz : (T)0;
-  auto store_tile = [&](int slot, const T* a, const T* b, int Kl) {
+  auto store_tile = [&](int slot, const T* a, const T* b) {
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       if (has(q)) {
         const T p = first ? a[q] : (T)2 * a[q] - b[q];
         sP[slot * HP + hE[q]] = p;
         sW[slot * HP + hE[q]] = (p * p * p - p) * icn2 - sc * p;
-        if (BT && (Kl == 0 || Kl == nz - 1)) {
-          const T ph = first ? a[q] : (T)2 * a[q] - (T)0.5 * b[q];
-          sB[(Kl == 0 ? 0 : HP) + hE[q]] = (Kl == 0 ? gb : gt) * ((T)1 - p * p) + kg * ph;
-        }
       }
     }
   };
@@ -140,6 +125,9 @@ __global__ void __launch_bounds__(kBlock)
     }
   };
   const T ihx2 = ihx * ihx, ihy2 = ihy * ihy, ihz2 = ihz * ihz, h = (T)0.5;
+  const T gb = (T)c.g_bot * ihz, gt = (T)c.g_top * ihz;
+  constexpr bool relax = RELAX;  // relaxed walls (eq. NS34 with D_w > 0)
+  const T kg = RELAX ? (T)(c.relax_kappa * c.inv_gamma0) * ihz : (T)0;
   auto phat_at = [&](int Kl, int Jl, int Il) -> T {
     const size_t id = ((size_t)Kl * ny + wrap(Jl, ny)) * nx + wrap(Il, nx);
     return first ? phin[id] : (T)2 * phin[id] - (T)0.5 * phinm1[id];
@@ -166,9 +154,9 @@ __global__ void __launch_bounds__(kBlock)
   T ta[R], tb[R];
   int sm = 0, s0 = 1, sp = 2;
   load_tile(K0 - 1, ta, tb);
-  store_tile(sm, ta, tb, K0 - 1);
+  store_tile(sm, ta, tb);
   load_tile(K0, ta, tb);
-  store_tile(s0, ta, tb, K0);
+  store_tile(s0, ta, tb);
   T phat_next = own_hat(ta, tb);
   load_tile(K0 + 1, ta, tb);
   T ufp = 0, ufm = 0, vfp = 0, vfm = 0, wk = 0, wkm = 0;
@@ -204,7 +192,7 @@ __global__ void __launch_bounds__(kBlock)
     }
     const T phat = phat_next;
     // layer K + 1 enters the ring; the layer after it and the next centre values go out
-    store_tile(sp, ta, tb, K + 1);
+    store_tile(sp, ta, tb);
     if (K + 1 < K0 + KB) {
       phat_next = own_hat(ta, tb);
       load_tile(K + 2, ta, tb);
@@ -236,18 +224,7 @@ __global__ void __launch_bounds__(kBlock)
       return b;
     };
     T lapb = 0;
-    if constexpr (BT) {
-      // the layer above a bottom (below a top) wall layer carries no data (nz >= 4)
-      if (K == 0 || K == nz - 1) {
-        const T* B = sB + (K == 0 ? 0 : HP) + c0;
-        const T b0 = B[0];
-        lapb = (B[1] - 2 * b0 + B[-1]) * ihx2 + (B[HX] - 2 * b0 + B[-HX]) * ihy2 - b0 * ihz2;
-      } else if (K == 1) {
-        lapb = sB[c0] * ihz2;
-      } else if (K == nz - 2) {
-        lapb = sB[HP + c0] * ihz2;
-      }
-    } else if (K == 0 || K == nz - 1) {
+    if (K == 0 || K == nz - 1) {
       const T b0 = bval(K, p0, relax ? phat_wall(K, J, I) : (T)0);
       lapb = (bval(K, pxp, relax ? phat_wall(K, J, I + 1) : (T)0) - 2 * b0 +
               bval(K, pxm, relax ? phat_wall(K, J, I - 1) : (T)0)) * ihx2 +
@@ -284,7 +261,9 @@ __global__ void __launch_bounds__(kBlock)
 // wavefronts per SIMD (80 registers, a few spilled): at 256 x 256 x 128 coarse cells that makes
 // one round of six blocks per CU with marches of 43 layers, measured 15% faster than five
 // wavefronts (one round of four blocks, marches of 64).
-template <typename T, int R, bool RELAX, int CXC = 0, bool MOVE = false>
+// INL: the relaxed walls' term of G formed with it (moving walls, and 2D grids, whose results stay
+// bitwise what they were).
+template <typename T, int R, bool RELAX, int CXC = 0, bool MOVE = false, bool INL = MOVE>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && R == 3 && !MOVE ? 6 : 1)))
     k_restrict_g(const T* __restrict__ phinew, const T* __restrict__ phin,
@@ -375,28 +354,30 @@ __global__ void __launch_bounds__(kBlock)
         T b = 0;
         if (K == 0) b += gb * ((T)1 - ps * ps);
         if (K == fnz - 1) b += gt * ((T)1 - ps * ps);
-        if (MOVE && (K == 0 || K == fnz - 1)) {
-          // relaxed walls: (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in the wall ghost, with
-          // phi_hat - dt u_w . grad phi* (eq. NS34) for moving walls, as in the right-hand side
+        if (RELAX && INL && (K == 0 || K == fnz - 1)) {
+          // relaxed walls: (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in the wall ghost
           const T an = ld_at(phin + K * layer, gOff[q]);
           T ph = first ? an : (T)2 * an - (T)0.5 * ld_at(phinm1 + K * layer, gOff[q]);
-          const int idx = (int)(gOff[q] / sizeof(T)), I = idx % fnx, J = idx / fnx;
-          const T* a = phin + K * layer;
-          const T* b1 = phinm1 + K * layer;
-          auto pst = [&](int jj, int ii) {
-            const int o = wrap(jj, fny) * fnx + wrap(ii, fnx);
-            return first ? a[o] : (T)2 * a[o] - b1[o];
-          };
-          const double* uw = K == 0 ? c.uwb : c.uwt;
-          const T adv = (T)uw[0] * (pst(J, I + 1) - pst(J, I - 1)) * ((T)0.5 * fihx) +
-                        (T)uw[1] * (pst(J + 1, I) - pst(J - 1, I)) * ((T)0.5 * fihy);
-          ph -= (T)c.dt * adv;
+          if constexpr (MOVE) {
+            // moving walls: phi_hat - dt u_w . grad phi* (eq. NS34), as in the right-hand side
+            const int idx = (int)(gOff[q] / sizeof(T)), I = idx % fnx, J = idx / fnx;
+            const T* a = phin + K * layer;
+            const T* b1 = phinm1 + K * layer;
+            auto pst = [&](int jj, int ii) {
+              const int o = wrap(jj, fny) * fnx + wrap(ii, fnx);
+              return first ? a[o] : (T)2 * a[o] - b1[o];
+            };
+            const double* uw = K == 0 ? c.uwb : c.uwt;
+            const T adv = (T)uw[0] * (pst(J, I + 1) - pst(J, I - 1)) * ((T)0.5 * fihx) +
+                          (T)uw[1] * (pst(J + 1, I) - pst(J - 1, I)) * ((T)0.5 * fihy);
+            ph -= (T)c.dt * adv;
+          }
           b += kg * ph - kk * p;
         }
         *(e < GP ? dst + e : sX + (e - GP)) = -cn2 * (lap + b) + S * (p - ps) + ps * ps * ps - ps;
       }
     }
-    if (RELAX && !MOVE && (K == 0 || K == fnz - 1)) {
+    if (RELAX && !INL && (K == 0 || K == fnz - 1)) {
       // relaxed walls at rest: the ghost's (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in a pass of
       // its own over the wall layers' G, a point at a time, so that the march keeps the
       // registers it has for static walls
@@ -547,7 +528,7 @@ __global__ void __launch_bounds__(256)
     k_weno_adv_zm(const T* __restrict__ phin, const T* __restrict__ phinm1, Prolonged<T> pv,
                   T* __restrict__ adv, int nx, int ny, int nz, int KB, T ihx, T ihy, T ihz) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr bool DIV = !Y3D && sizeof(T) == 8;  // see weno_face_div
+  constexpr bool DIV = !Y3D;  // see weno_face_div
   const int TX = blockDim.x, TY = blockDim.y;
   int bx, by, bz;
   xcd_tile(bx, by, bz);
@@ -805,8 +786,7 @@ hipError_t launch_ch_rhs(const Dims& f, const Dims& c, const StepConsts& k, ChIn
   const int HP = (TX + 2) * (TY + 2);
   const int need = (HP + TX * TY - 1) / (TX * TY);
   if (need > 4) return hipErrorInvalidConfiguration;
-  // three slots each of phi* and w*, and the wall data of relaxed walls
-  const size_t shm = (size_t)(k.relax_kappa != 0.0 ? 8 : 6) * HP * sizeof(T);
+  const size_t shm = (size_t)6 * HP * sizeof(T);
   const dim3 grid(f.nx / TX, f.ny / TY, f.nz / KB), block(TX, TY, 1);
 #define DRPF_CH(R, MODE, RELAX, TXC, ...)                                                          \
   hipLaunchKernelGGL((k_ch_rhs<T, R, MODE, RELAX, TXC, ##__VA_ARGS__>), grid, block, shm, st, in.phin, \
@@ -873,7 +853,9 @@ hipError_t launch_restrict_g(const Dims& f, const Dims& c, const StepConsts& k, 
   if (k.relax_kappa != 0.0 && moving) {
     if (Rk == 3) go(k_restrict_g<T, 3, true, 0, true>); else go(k_restrict_g<T, 6, true, 0, true>);
   } else if (k.relax_kappa != 0.0) {
-    if (CX == 32 && CY == 4) go(k_restrict_g<T, 3, true, 32>);
+    if (ry == 1) {
+      if (Rk == 3) go(k_restrict_g<T, 3, true, 0, false, true>); else go(k_restrict_g<T, 6, true, 0, false, true>);
+    } else if (CX == 32 && CY == 4) go(k_restrict_g<T, 3, true, 32>);
     else if (Rk == 3) go(k_restrict_g<T, 3, true>);
     else go(k_restrict_g<T, 6, true>);
   } else {

@@ -501,7 +501,7 @@ struct TauOut {
   T* p[6];
 };
 
-// DIV: the WENO-Z face values in the form of weno_face_div (2D FP64 grids).
+// DIV: the WENO-Z face values in the form of weno_face_div (2D grids).
 template <typename T, bool WENO, bool DIV = false>
 __global__ void __launch_bounds__(kBlock)
     k_polymer_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w,
@@ -928,8 +928,8 @@ hipError_t launch_polymer_stage(const Dims& c, const StepConsts& k, const T* u, 
   };
   if (k.advection != 1)
     go(k_polymer_stage<T, false>);
-  else if (sizeof(T) == 8 && c.ny == 1)
-    go(k_polymer_stage<T, true, sizeof(T) == 8>);
+  else if (c.ny == 1)
+    go(k_polymer_stage<T, true, true>);
   else
     go(k_polymer_stage<T, true>);
   return hipGetLastError();

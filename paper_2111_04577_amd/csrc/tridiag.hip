@@ -243,6 +243,9 @@ __global__ void __launch_bounds__(256)
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < layer; e += gridDim.x * blockDim.x) x[base + e] = top[e];
 }
 
+// the walls of the Cahn-Hilliard pass, and which form of the relaxed walls' correction
+constexpr int kEquilibrium = 0, kRelaxed = 1, kRelaxedOrdered = 2;
+
 // Relaxed walls (eq. NS34 with D_w > 0): the operator is (L - c_psi)(L + alpha) + L dW, d = dwall
 // on the two wall-adjacent rows, a rank-two change of the Neumann product that the DCT
 // diagonalises. With F0 = X / A (A = (lambda - c_psi)(lambda + alpha), X the DCT of the
@@ -259,11 +262,10 @@ __global__ void __launch_bounds__(256)
 // registers from the sums to the correction; the sums (FP64) are reduced across the lanes of
 // each wavefront and then over the wavefronts through LDS (part: 6 TL doubles per wavefront), one
 // barrier in all. With F0, G and the partial sums in LDS and five barriers the pass took 73 us at
-// 256 x 256 x 128, FP64. coef(m, mr, t, ...) forms F0, lambda and 1 / A at m and mr = N - m from
-// the forward transform; store(m, mr, t, Fm, Fr) writes the inverse's input.
-template <typename T, bool TRANS, int NI, typename Coef, typename Store>
+// 256 x 256 x 128, FP64. at(m, t): place m of the forward transform; coef forms F0, lambda and 1 / A; store(m, mr, t, Fm, Fr) writes the inverse's input.
+template <typename T, bool TRANS, int NI, typename At, typename Coef, typename Store>
 __device__ __forceinline__ void relaxed_walls(int Nz, int TL, int ltl, const cx<T>* __restrict__ twq, T dwall,
-                                              double* part, Coef&& coef, Store&& store) {
+                                              double* part, At&& at, Coef&& coef, Store&& store) {
   const int half = Nz >> 1, t = threadIdx.x & (TL - 1), nth = blockDim.x;
   const T dn = dwall / (T)Nz;
   cx<T> Fm[NI], Fr[NI];
@@ -286,8 +288,10 @@ __device__ __forceinline__ void relaxed_walls(int Nz, int TL, int ltl, const cx<
     if (e < (half + 1) * TL) {
       const int m = e >> ltl, mr = (Nz - m) & (Nz - 1);
       const cx<T> wm = twq[m], wr = twq[mr];
+      const cx<T> Vm = at(m, t), Vr = at(mr, t);
       T lm, im, lr, ir;
-      coef(m, mr, t, wm, wr, Fm[i], Fr[i], lm, im, lr, ir);
+      Fm[i] = coef(m, Vm, Vr, wm, lm, im);
+      Fr[i] = coef(mr, Vr, Vm, wr, lr, ir);
       Gm[i] = dn * (TRANS ? (T)1 : lm) * wm.re * im;
       Gr[i] = dn * (TRANS ? (T)1 : lr) * wr.re * ir;
       add(m, wm.re, lm, Fm[i], Gm[i]);
@@ -327,6 +331,75 @@ __device__ __forceinline__ void relaxed_walls(int Nz, int TL, int ltl, const cx<
   }
 }
 
+// The same correction with the sums in the order of m (chunks of a stride, then the chunks) and
+// the coefficients in LDS: 2D grids. A viscoelastic 2D run carries a velocity normal to its plane
+// that is round-off of the stresses (1e-20), whose value hangs on every bit upstream; 2D results
+// stay bitwise what they were, and a 2D pass is bound by launch and latency (256 x 1 x 128 coarse
+// cells: 5 us of a step of 72). at(m, t): the coefficient's place; lam(m): lambda_m of the thread's mode.
+template <typename T, bool TRANS, typename At, typename Lam, typename Coef, typename Store>
+__device__ __forceinline__ void relaxed_walls_ordered(int Nz, int TL, int ltl, const cx<T>* __restrict__ twq, T dwall,
+                                                      unsigned char* lds, At&& at, Lam&& lam, Coef&& coef, Store&& store) {
+  const int half = Nz >> 1;
+  const int NC = min((int)(blockDim.x >> ltl), 16);
+  cx<double>* sd = reinterpret_cast<cx<double>*>(lds);
+  double* part = reinterpret_cast<double*>(sd + 2 * TL);
+  T* sG = reinterpret_cast<T*>(part + 6 * NC * TL);
+  for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
+    const int m = e >> ltl, t = e & (TL - 1), mr = (Nz - m) & (Nz - 1);
+    const cx<T> Vm = at(m, t), Vr = at(mr, t);
+    T lm, im;
+    at(m, t) = coef(m, Vm, Vr, twq[m], lm, im);
+    sG[m * TL + t] = dwall * (TRANS ? (T)1 : lm) * twq[m].re * im / (T)Nz;
+    if (mr != m) {
+      T lr, ir;
+      at(mr, t) = coef(mr, Vr, Vm, twq[mr], lr, ir);
+      sG[mr * TL + t] = dwall * (TRANS ? (T)1 : lr) * twq[mr].re * ir / (T)Nz;
+    }
+  }
+  __syncthreads();
+  // partial sums over m = ch, ch + NC, ... per mode, then their totals
+  for (int e = threadIdx.x; e < NC * TL; e += blockDim.x) {
+    const int t = e & (TL - 1), ch = e >> ltl;
+    double acc[6] = {0, 0, 0, 0, 0, 0};  // P_e (re, im), P_o (re, im), H_e, H_o
+    for (int m = ch; m < Nz; m += NC) {
+      const double wc = (m == 0 ? 2.0 : 4.0) * (double)twq[m].re * (TRANS ? (double)lam(m) : 1.0);
+      const cx<T> F = at(m, t);
+      const int o = (m & 1) * 2;
+      acc[o] += wc * (double)F.re;
+      acc[o + 1] += wc * (double)F.im;
+      acc[4 + (m & 1)] += wc * (double)sG[m * TL + t];
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) part[(ch * TL + t) * 6 + q] = acc[q];
+  }
+  __syncthreads();
+  // totals: one thread per (quantity, mode), into the first chunk's slots
+  for (int e = threadIdx.x; e < 6 * TL; e += blockDim.x) {
+    const int t = e % TL, q = e / TL;
+    double a = 0;
+    for (int ch = 0; ch < NC; ++ch) a += part[(ch * TL + t) * 6 + q];
+    part[t * 6 + q] = a;
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < TL; t += blockDim.x) {
+    const double* a = part + t * 6;
+    sd[2 * t] = mk<double>(a[0] / (1.0 + a[4]), a[1] / (1.0 + a[4]));      // sigma
+    sd[2 * t + 1] = mk<double>(a[2] / (1.0 + a[5]), a[3] / (1.0 + a[5]));  // delta
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
+    const int m = e >> ltl, t = e & (TL - 1), mr = (Nz - m) & (Nz - 1);
+    auto corrected = [&](int mm) -> cx<T> {
+      const cx<T> F = at(mm, t);
+      const cx<double> s = sd[2 * t + (mm & 1)];
+      const double g = (double)sG[mm * TL + t];
+      return mk<T>((T)((double)F.re - g * s.re), (T)((double)F.im - g * s.im));
+    };
+    const cx<T> Fm = corrected(m);
+    store(m, mr, t, Fm, mr != m ? corrected(mr) : Fm);
+  }
+}
+
 // ---- Cahn-Hilliard pair -------------------------------------------------------------
 // Both CH operators have zero-flux walls, so the DCT-II across the walls diagonalises them
 // exactly (eigenvalue lam_z(m) of the second difference for cos(pi m (k + 1/2) / nz)). The
@@ -338,7 +411,7 @@ __device__ __forceinline__ void relaxed_walls(int Nz, int TL, int ltl, const cx<
 // from the pair (V_m, V_{nz-m}). A block holds TL consecutive modes, each a line of the
 // compile-time FFT form (lds_fft16.hpp), which serves FP32; k_zpass_ch_rt below is the same
 // pass with the run-time form (lds_fft.hpp, columns in LDS), which serves FP64.
-template <typename T, bool ROBIN, int LOGNZ>
+template <typename T, int W, int LOGNZ>
 __global__ void __launch_bounds__(kZBlock)
     k_zpass_ch(cx<T>* __restrict__ S, int P, int Ny, int TL,
                const double* __restrict__ lamx, const double* __restrict__ lamy,
@@ -385,7 +458,7 @@ __global__ void __launch_bounds__(kZBlock)
       at(m, t) = conj(twq[m]) * mk<T>(Fm.re + Fm.im, Fm.im - Fm.re);
     }
   };
-  if (!ROBIN) {
+  if constexpr (W == kEquilibrium) {
     for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
       const int m = e >> ltl, t = e & (TL - 1);
       const int l = min(l0 + t, lines - 1);
@@ -412,18 +485,17 @@ __global__ void __launch_bounds__(kZBlock)
     const T lxy = (T)(lamx[kx] + lamy[ky]);
     // after the twiddles, rounded up to 16 bytes: the wavefronts' partial sums
     const size_t so = ((size_t)(TL * F::LS + Nz) * sizeof(cx<T>) + 15) & ~(size_t)15;
-    relaxed_walls<T, false, 5>(
-        Nz, TL, ltl, twq, (T)dwall, reinterpret_cast<double*>(smem + so),
-        [&](int m, int mr, int t, cx<T> wm, cx<T> wr, cx<T>& Fm, cx<T>& Fr, T& lm, T& im, T& lr, T& ir) {
-          const cx<T> Vm = at(m, t), Vr = at(mr, t);
-          lm = lxy + (T)lamz[m];
-          im = recip((lm - cp) * (lm + al));
-          Fm = (sc * im) * dct_out(Vm, Vr, wm);
-          lr = lxy + (T)lamz[mr];
-          ir = recip((lr - cp) * (lr + al));
-          Fr = (sc * ir) * dct_out(Vr, Vm, wr);
-        },
-        inverse_in);
+    // F0, lambda and 1 / A of coefficient m from V_m, V_{N-m}
+    auto coef = [&](int m, cx<T> V, cx<T> Vp, cx<T> w, T& lam, T& inv) -> cx<T> {
+      lam = lxy + (T)lamz[m];
+      inv = recip((lam - cp) * (lam + al));
+      return (sc * inv) * dct_out(V, Vp, w);
+    };
+    if constexpr (W == kRelaxed)
+      relaxed_walls<T, false, 5>(Nz, TL, ltl, twq, (T)dwall, reinterpret_cast<double*>(smem + so), at, coef, inverse_in);
+    else
+      relaxed_walls_ordered<T, false>(Nz, TL, ltl, twq, (T)dwall, smem + so, at,
+                                      [&](int m) { return lxy + (T)lamz[m]; }, coef, inverse_in);
   }
   __syncthreads();
   fft16<T, true, LOGNZ, fft_lp<T>()>(buf + fb * F::LS, fq, fb < TL, stw);
@@ -437,7 +509,7 @@ __global__ void __launch_bounds__(kZBlock)
 
 // The same pass with the transform length at run time (lds_fft): the FP64 form. TRANS (relaxed
 // walls only) solves with the transposed operator, for the discrete adjoint.
-template <typename T, bool ROBIN, bool TRANS = false>
+template <typename T, int W, bool TRANS = false>
 __global__ void __launch_bounds__(1024)
     k_zpass_ch_rt(cx<T>* __restrict__ S, int P, int Ny, int Nz, int logNz, int TL,
                const double* __restrict__ lamx, const double* __restrict__ lamy,
@@ -480,7 +552,7 @@ __global__ void __launch_bounds__(1024)
       buf[m * TL + t] = conj(twq[m]) * mk<T>(Fm.re + Fm.im, Fm.im - Fm.re);
     }
   };
-  if (!ROBIN) {
+  if constexpr (W == kEquilibrium) {
     for (int e = threadIdx.x; e < (half + 1) * TL; e += blockDim.x) {
       const int m = e >> ltl, t = e & (TL - 1);
       const int l = min(l0 + t, lines - 1);
@@ -507,18 +579,18 @@ __global__ void __launch_bounds__(1024)
     const T lxy = (T)(lamx[kx] + lamy[ky]);
     // after the twiddles, rounded up to 16 bytes: the wavefronts' partial sums
     const size_t so = ((size_t)(Nz * TL + Nz) * sizeof(cx<T>) + 15) & ~(size_t)15;
-    relaxed_walls<T, TRANS, 3>(
-        Nz, TL, ltl, twq, (T)dwall, reinterpret_cast<double*>(smem + so),
-        [&](int m, int mr, int t, cx<T> wm, cx<T> wr, cx<T>& Fm, cx<T>& Fr, T& lm, T& im, T& lr, T& ir) {
-          const cx<T> Vm = buf[m * TL + t], Vr = buf[mr * TL + t];
-          lm = lxy + (T)lamz[m];
-          im = recip((lm - cp) * (lm + al));
-          Fm = (sc * im) * dct_out(Vm, Vr, wm);
-          lr = lxy + (T)lamz[mr];
-          ir = recip((lr - cp) * (lr + al));
-          Fr = (sc * ir) * dct_out(Vr, Vm, wr);
-        },
-        inverse_in);
+    // F0, lambda and 1 / A of coefficient m from V_m, V_{N-m}
+    auto coef = [&](int m, cx<T> V, cx<T> Vp, cx<T> w, T& lam, T& inv) -> cx<T> {
+      lam = lxy + (T)lamz[m];
+      inv = recip((lam - cp) * (lam + al));
+      return (sc * inv) * dct_out(V, Vp, w);
+    };
+    auto at = [&](int m, int t) -> cx<T>& { return buf[m * TL + t]; };
+    if constexpr (W == kRelaxed)
+      relaxed_walls<T, TRANS, 3>(Nz, TL, ltl, twq, (T)dwall, reinterpret_cast<double*>(smem + so), at, coef, inverse_in);
+    else
+      relaxed_walls_ordered<T, TRANS>(Nz, TL, ltl, twq, (T)dwall, smem + so, at,
+                                      [&](int m) { return lxy + (T)lamz[m]; }, coef, inverse_in);
   }
   __syncthreads();
   lds_fft<T, true, true>(buf, Nz, logNz, TL, ltl, stw);
@@ -809,13 +881,18 @@ hipError_t launch_zpass_ch(const Dims& d, const Tables<T>& tb, cx<T>* spec, doub
     size_t shm = (size_t)d.nz * (TL + 1) * sizeof(cx<T>);
     // the inverse transforms are unnormalised: fold 1/nz into the spectral scale
     if (dwall == 0.0) {
-      hipLaunchKernelGGL((k_zpass_ch_rt<T, false>), dim3((lines + TL - 1) / TL), dim3(threads), shm, st, spec,
+      hipLaunchKernelGGL((k_zpass_ch_rt<T, kEquilibrium>), dim3((lines + TL - 1) / TL), dim3(threads), shm, st, spec,
                          d.pitch, d.ny, d.nz, lognz, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi,
                          alpha, scale / d.nz, 0.0);
     } else {
-      // relaxed walls: 6 partial sums per mode and wavefront
-      shm = ((shm + 15) & ~(size_t)15) + (size_t)6 * (threads / 64) * TL * sizeof(double);
-      auto kern = trans ? k_zpass_ch_rt<T, true, true> : k_zpass_ch_rt<T, true, false>;
+      // relaxed walls: 6 partial sums per mode and wavefront; 2D: those of relaxed_walls_ordered
+      const int nc = threads / TL < 16 ? threads / TL : 16;
+      shm = ((shm + 15) & ~(size_t)15) +
+            (d.ny > 1 ? (size_t)6 * (threads / 64) * TL * sizeof(double)
+                      : (size_t)2 * TL * sizeof(cx<double>) + (size_t)6 * nc * TL * sizeof(double) + (size_t)d.nz * TL * sizeof(T));
+      constexpr int R3 = kRelaxed, R2 = kRelaxedOrdered;
+      auto kern = d.ny > 1 ? (trans ? k_zpass_ch_rt<T, R3, true> : k_zpass_ch_rt<T, R3, false>)
+                           : (trans ? k_zpass_ch_rt<T, R2, true> : k_zpass_ch_rt<T, R2, false>);
       hipLaunchKernelGGL(kern, dim3((lines + TL - 1) / TL), dim3(threads), shm, st, spec, d.pitch, d.ny, d.nz,
                          lognz, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi, alpha, scale / d.nz,
                          dwall);
@@ -838,13 +915,17 @@ hipError_t launch_zpass_ch(const Dims& d, const Tables<T>& tb, cx<T>* spec, doub
       using F = FftPlan<LOGNZ, fft_lp<T>()>;
       size_t shm = ((size_t)TL * F::LS + F::M) * sizeof(cx<T>);
       if (dwall == 0.0) {
-        hipLaunchKernelGGL((k_zpass_ch<T, false, LOGNZ>), dim3((lines + TL - 1) / TL), dim3(threads), shm, st,
+        hipLaunchKernelGGL((k_zpass_ch<T, kEquilibrium, LOGNZ>), dim3((lines + TL - 1) / TL), dim3(threads), shm, st,
                            spec, d.pitch, d.ny, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi, alpha,
                            scale / d.nz, 0.0);
       } else {
-        // relaxed walls: 6 partial sums per mode and wavefront
-        shm = ((shm + 15) & ~(size_t)15) + (size_t)6 * ((threads + 63) / 64) * TL * sizeof(double);
-        hipLaunchKernelGGL((k_zpass_ch<T, true, LOGNZ>), dim3((lines + TL - 1) / TL), dim3(threads), shm, st,
+        // relaxed walls: 6 partial sums per mode and wavefront; 2D: those of relaxed_walls_ordered
+        const int nc = threads / TL < 16 ? threads / TL : 16;
+        shm = ((shm + 15) & ~(size_t)15) +
+              (d.ny > 1 ? (size_t)6 * ((threads + 63) / 64) * TL * sizeof(double)
+                        : (size_t)2 * TL * sizeof(cx<double>) + (size_t)6 * nc * TL * sizeof(double) + (size_t)d.nz * TL * sizeof(T));
+        auto kern = d.ny > 1 ? k_zpass_ch<T, kRelaxed, LOGNZ> : k_zpass_ch<T, kRelaxedOrdered, LOGNZ>;
+        hipLaunchKernelGGL(kern, dim3((lines + TL - 1) / TL), dim3(threads), shm, st,
                            spec, d.pitch, d.ny, TL, tb.lam_x, tb.lam_y, tb.lam_z, tb.tw_z, tb.tw_zq, c_psi, alpha,
                            scale / d.nz, dwall);
       }

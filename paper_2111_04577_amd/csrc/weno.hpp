@@ -52,11 +52,12 @@ __device__ __forceinline__ T weno_face(T vm2, T vm1, T v0, T vp1, T vp2) {
 __device__ __forceinline__ double wdiv(double a, double b) { return a / b; }
 __device__ __forceinline__ float wdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
-// The same value with every quotient a division of its own: the form of the 2D FP64 kernels and
-// of the reverse pass. The reverse pass differentiates the weights; where the field is flat to
-// round-off their derivatives turn a change in the last bit of the forward values into 4e-7 of the
-// gradient, so gradient runs (2D, FP64) keep their forward arithmetic, and the reverse kernels the
-// arithmetic they differentiate. A 2D step is bound by launches and latency, not by this.
+// The same value with every quotient a division of its own: the form of the 2D grids and of the
+// reverse pass. The reverse pass differentiates the weights; where the field is flat to round-off
+// their derivatives turn a change in the last bit of the forward values into 4e-7 of the gradient,
+// and the velocity normal to the plane of a viscoelastic 2D run is round-off that hangs on every
+// bit upstream. So 2D runs keep their arithmetic, and the reverse kernels the arithmetic they
+// differentiate. A 2D step is bound by launches and latency, not by this.
 template <typename T>
 __device__ __forceinline__ T weno_face_div(T vm2, T vm1, T v0, T vp1, T vp2) {
   const T eps = sizeof(T) == 8 ? (T)1e-40 : (T)1e-30;
