@@ -39,13 +39,6 @@ __device__ __forceinline__ Vec<T, N> ld_vec(const T* base, unsigned byte_off) {
   return r;
 }
 
-// An opaque value: keeps the compiler from fusing its last operation into a later one.
-template <typename T>
-__device__ __forceinline__ T opaque(T x) {
-  asm("" : "+v"(x));
-  return x;
-}
-
 // LOGM: log2(nx / 2) at compile time (FP32), 0 = run-time length (FP64). MODE: 0 dual
 // resolution, 1 single resolution, 2 advection given (WENO-Z). RELAX: relaxed walls at rest.
 template <typename T, int LOGM, int MODE, bool RELAX, bool Y3D>

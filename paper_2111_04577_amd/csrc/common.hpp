@@ -144,6 +144,13 @@ __device__ __forceinline__ void xcd_tile(int& bx, int& by, int& bz) {
   bz = t / (gx * gy);
 }
 
+// An opaque value: keeps the compiler from fusing its last operation into a later one.
+template <typename T>
+__device__ __forceinline__ T opaque(T x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
 // Layers per block of a z-marching launch over `cols` column tiles: as many blocks as the
 // device holds at once (one round, no tail of late blocks), each marching ceil(nz / blocks per
 // column) layers.

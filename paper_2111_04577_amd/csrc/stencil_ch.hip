@@ -261,9 +261,7 @@ __global__ void __launch_bounds__(kBlock)
 // wavefronts per SIMD (80 registers, a few spilled): at 256 x 256 x 128 coarse cells that makes
 // one round of six blocks per CU with marches of 43 layers, measured 15% faster than five
 // wavefronts (one round of four blocks, marches of 64).
-// INL: the relaxed walls' term of G formed with it (moving walls, and 2D grids, whose results stay
-// bitwise what they were).
-template <typename T, int R, bool RELAX, int CXC = 0, bool MOVE = false, bool INL = MOVE>
+template <typename T, int R, bool RELAX, int CXC = 0, bool MOVE = false>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && R == 3 && !MOVE ? 6 : 1)))
     k_restrict_g(const T* __restrict__ phinew, const T* __restrict__ phin,
@@ -354,30 +352,28 @@ __global__ void __launch_bounds__(kBlock)
         T b = 0;
         if (K == 0) b += gb * ((T)1 - ps * ps);
         if (K == fnz - 1) b += gt * ((T)1 - ps * ps);
-        if (RELAX && INL && (K == 0 || K == fnz - 1)) {
-          // relaxed walls: (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in the wall ghost
+        if (MOVE && (K == 0 || K == fnz - 1)) {
+          // relaxed walls: (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in the wall ghost, with
+          // phi_hat - dt u_w . grad phi* (eq. NS34) for moving walls, as in the right-hand side
           const T an = ld_at(phin + K * layer, gOff[q]);
           T ph = first ? an : (T)2 * an - (T)0.5 * ld_at(phinm1 + K * layer, gOff[q]);
-          if constexpr (MOVE) {
-            // moving walls: phi_hat - dt u_w . grad phi* (eq. NS34), as in the right-hand side
-            const int idx = (int)(gOff[q] / sizeof(T)), I = idx % fnx, J = idx / fnx;
-            const T* a = phin + K * layer;
-            const T* b1 = phinm1 + K * layer;
-            auto pst = [&](int jj, int ii) {
-              const int o = wrap(jj, fny) * fnx + wrap(ii, fnx);
-              return first ? a[o] : (T)2 * a[o] - b1[o];
-            };
-            const double* uw = K == 0 ? c.uwb : c.uwt;
-            const T adv = (T)uw[0] * (pst(J, I + 1) - pst(J, I - 1)) * ((T)0.5 * fihx) +
-                          (T)uw[1] * (pst(J + 1, I) - pst(J - 1, I)) * ((T)0.5 * fihy);
-            ph -= (T)c.dt * adv;
-          }
+          const int idx = (int)(gOff[q] / sizeof(T)), I = idx % fnx, J = idx / fnx;
+          const T* a = phin + K * layer;
+          const T* b1 = phinm1 + K * layer;
+          auto pst = [&](int jj, int ii) {
+            const int o = wrap(jj, fny) * fnx + wrap(ii, fnx);
+            return first ? a[o] : (T)2 * a[o] - b1[o];
+          };
+          const double* uw = K == 0 ? c.uwb : c.uwt;
+          const T adv = (T)uw[0] * (pst(J, I + 1) - pst(J, I - 1)) * ((T)0.5 * fihx) +
+                        (T)uw[1] * (pst(J + 1, I) - pst(J - 1, I)) * ((T)0.5 * fihy);
+          ph -= (T)c.dt * adv;
           b += kg * ph - kk * p;
         }
         *(e < GP ? dst + e : sX + (e - GP)) = -cn2 * (lap + b) + S * (p - ps) + ps * ps * ps - ps;
       }
     }
-    if (RELAX && !INL && (K == 0 || K == fnz - 1)) {
+    if (RELAX && !MOVE && (K == 0 || K == fnz - 1)) {
       // relaxed walls at rest: the ghost's (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in a pass of
       // its own over the wall layers' G, a point at a time, so that the march keeps the
       // registers it has for static walls
@@ -514,6 +510,123 @@ __global__ void __launch_bounds__(kBlock)
     }
   }
 }
+// The same for 2D grids (one cell in y). The march above would load every phi row four times and
+// evaluate G twice (its tile carries y neighbours), in a chain of one barrier round per coarse layer,
+// on a handful of blocks: 2D passes are bound by latency. Here a block takes BX columns of one coarse
+// layer (two layers, which share halo layers, gain 0.4% of a step at 512 x 256 coarse cells): every
+// load (phi^{n+1} with a one-cell halo, phi*) goes out at once and into LDS, G is evaluated in place
+// of phi*, then four threads per cell form the restricted sums: two barriers in all. The sums are
+// the march's, term by term: with equal y rows its y differences vanish and its y pairs are
+// the doubled row. FP64, 256 x 128 fine cells: 10.7 us by the march, 6.1 us so.
+template <typename T, bool RELAX>
+__global__ void __launch_bounds__(128)
+    k_restrict_g_2d(const T* __restrict__ phinew, const T* __restrict__ phin, const T* __restrict__ phinm1,
+                    Restricted<T> r, int fnx, int fnz, T fihx, T fihz, int cnx, int cnz, int BX, StepConsts c) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int nbx = cnx / BX;
+  const int i0 = ((int)blockIdx.x % nbx) * BX, k = (int)blockIdx.x / nbx;
+  const int GX = 2 * BX + 1, PX = GX + 2;
+  const int NP = 5 * PX, NG = 3 * GX;
+  T* sP = reinterpret_cast<T*>(smem);  // phi^{n+1}, fine layers 2 k - 1 .. 2 k + 3
+  T* sG = sP + NP;                     // phi*, then G, fine layers 2 k .. 2 k + 2
+  const int tid = threadIdx.x, nth = blockDim.x;
+  const bool first = c.first != 0;
+  const T ihx2 = fihx * fihx, ihz2 = fihz * fihz;
+  const T cn2 = (T)c.cn2, S = (T)c.S;
+  const T gb = (T)c.g_bot * fihz, gt = (T)c.g_top * fihz;
+  const T kk = RELAX ? (T)c.relax_kappa * fihz : (T)0;
+  const T kg = RELAX ? (T)(c.relax_kappa * c.inv_gamma0) * fihz : (T)0;
+  const int X0 = 2 * i0, Z0 = 2 * k;
+  auto kc = [&](int Kf) { return min(max(Kf, 0), fnz - 1); };
+  auto col = [&](int x) { return x < 0 ? x + fnx : (x >= fnx ? x - fnx : x); };
+  // every load of the block in flight before the first is used
+  constexpr int BXM = 32, LP = (5 * (2 * BXM + 3) + 127) / 128, LG = (3 * (2 * BXM + 1) + 127) / 128;
+  T vp[LP], va[LG], vb[LG];
+#pragma unroll
+  for (int q = 0; q < LP; ++q) {
+    const int e = min(tid + q * nth, NP - 1), l = e / PX, x = e - l * PX;
+    vp[q] = phinew[kc(Z0 - 1 + l) * fnx + col(X0 - 1 + x)];
+  }
+#pragma unroll
+  for (int q = 0; q < LG; ++q) {
+    const int e = min(tid + q * nth, NG - 1), l = e / GX, x = e - l * GX;
+    const int id = kc(Z0 + l) * fnx + col(X0 + x);
+    va[q] = phin[id];
+    vb[q] = phinm1[id];
+  }
+#pragma unroll
+  for (int q = 0; q < LP; ++q)
+    if (tid + q * nth < NP) sP[tid + q * nth] = vp[q];
+#pragma unroll
+  for (int q = 0; q < LG; ++q)
+    if (tid + q * nth < NG) sG[tid + q * nth] = first ? va[q] : (T)2 * va[q] - vb[q];
+  __syncthreads();
+  for (int e = tid; e < NG; e += nth) {
+    const int l = e / GX, x = e - l * GX;
+    const int K = Z0 + l;
+    if (K >= fnz) break;  // beyond the top wall: read as the layer below
+    const T* P0 = sP + (l + 1) * PX + x + 1;
+    const T p = P0[0];
+    const T lap = fma(P0[PX] - 2 * p + P0[-PX], ihz2, (P0[1] - 2 * p + P0[-1]) * ihx2);
+    const T ps = sG[e];
+    T b = 0;
+    if (K == 0 || K == fnz - 1) {
+      // wetting data, rounded before the wall term is added (the march's order of operations)
+      b = opaque((K == 0 ? gb : gt) * fma(-ps, ps, (T)1));
+      if (RELAX) {
+        // relaxed walls: (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in the wall ghost
+        const int id = K * fnx + col(X0 + x);
+        const T an = phin[id];
+        const T ph = first ? an : (T)2 * an - (T)0.5 * phinm1[id];
+        b += fma(kg, ph, -(kk * p));
+      }
+    }
+    sG[e] = -cn2 * (lap + b) + S * (p - ps) + ps * ps * ps - ps;
+  }
+  __syncthreads();
+  const T r1 = (T)c.rho1, r2 = (T)c.rho2, m1 = (T)c.mu1, m2 = (T)c.mu2, hf = (T)0.5;
+  auto rinv = [&](T ph) { return (T)1 / (hf * ((T)1 + ph) * r1 + hf * ((T)1 - ph) * r2); };
+  auto mu = [&](T ph) { return hf * ((T)1 + ph) * m1 + hf * ((T)1 - ph) * m2; };
+  // four threads per coarse cell: the G set, and phi at the centre, the x face and the z face
+  for (int e = tid; e < 4 * BX; e += nth) {
+    const int x = e % BX, role = e / BX;
+    T c_[3], f_[3];  // x sums over the centre pair and the face pair, doubled (the single y cell twice)
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz) {
+      const int l = kc(2 * k + dz) - Z0;
+      const T* pr = role == 0 ? sG + l * GX + 2 * x : sP + (l + 1) * PX + 2 * x + 1;
+      c_[dz] = (T)2 * (pr[0] + pr[1]);
+      f_[dz] = (T)2 * (pr[1] + pr[2]);
+    }
+    const T e8 = (T)0.125;
+    const int id = k * cnx + i0 + x;
+    const T cc = e8 * (c_[0] + c_[1]), cf = e8 * (f_[0] + f_[1]), cz = e8 * (c_[1] + c_[2]);
+    if (role == 0) {
+      r.G_c[id] = cc;
+      r.G_x[id] = cf;
+      r.G_y[id] = cc;
+      r.G_z[id] = cz;
+    } else {
+      const T v = role == 1 ? cc : (role == 2 ? cf : cz);
+      const T ri = rinv(v), m = mu(v);
+      if (role == 1) {
+        r.phi_c[id] = v;
+        r.ri_y[id] = ri;
+        r.mu_c[id] = m;
+      } else if (role == 2) {
+        r.ri_x[id] = ri;
+        r.mu_xy[id] = m;
+        r.mu_xz[id + cnx] = mu(e8 * (f_[1] + f_[2]));  // z edges: layer k + 1 is the edge at (k + 1) hz
+        if (k == 0) r.mu_xz[id] = mu((T)0.25 * f_[0]);
+      } else {
+        r.ri_z[id] = ri;
+        r.mu_yz[id + cnx] = m;
+        if (k == 0) r.mu_yz[id] = mu((T)0.25 * c_[0]);
+      }
+    }
+  }
+}
+
 // div(u_f phi*) on the fine grid with WENO-Z face values (the advection of eq. NS25), phi* =
 // 2 phi^n - phi^{n-1} (phi^n on the first step), face velocities prolonged on the fly (eq.
 // dual1; as they are at a single resolution). A z-march that evaluates every face once: a
@@ -825,6 +938,17 @@ template <typename T>
 hipError_t launch_restrict_g(const Dims& f, const Dims& c, const StepConsts& k, const T* phinew,
                              const T* phin, const T* phinm1, Restricted<T> r, hipStream_t st) {
   const int ry = c.ny == 1 ? 1 : 2;
+  const bool moving = k.uwb[0] != 0.0 || k.uwb[1] != 0.0 || k.uwt[0] != 0.0 || k.uwt[1] != 0.0;
+  const bool relax = k.relax_kappa != 0.0;
+  // 2D but for moving relaxed walls, whose wall term reads phi* around the wall cells
+  if (ry == 1 && !(relax && moving)) {
+    const int BX = c.nx < 32 ? c.nx : 32;
+    const size_t shm = (size_t)(5 * (2 * BX + 3) + 3 * (2 * BX + 1)) * sizeof(T);
+    auto kernel = relax ? k_restrict_g_2d<T, true> : k_restrict_g_2d<T, false>;
+    hipLaunchKernelGGL(kernel, dim3((c.nx / BX) * c.nz), dim3(128), shm, st, phinew, phin, phinm1, r, f.nx, f.nz,
+                       (T)f.ihx, (T)f.ihz, c.nx, c.nz, BX, k);
+    return hipGetLastError();
+  }
   int CX, CY;
   if (ry == 2) {
     CX = c.nx < 32 ? c.nx : 32;
@@ -849,13 +973,10 @@ hipError_t launch_restrict_g(const Dims& f, const Dims& c, const StepConsts& k, 
     hipLaunchKernelGGL(kernel, grid, block, shm, st, phinew, phin, phinm1, r, f.nx, f.ny, f.nz, (T)f.ihx,
                        (T)f.ihy, (T)f.ihz, c.nx, c.ny, c.nz, ry, KB, k);
   };
-  const bool moving = k.uwb[0] != 0.0 || k.uwb[1] != 0.0 || k.uwt[0] != 0.0 || k.uwt[1] != 0.0;
-  if (k.relax_kappa != 0.0 && moving) {
+  if (relax && moving) {
     if (Rk == 3) go(k_restrict_g<T, 3, true, 0, true>); else go(k_restrict_g<T, 6, true, 0, true>);
-  } else if (k.relax_kappa != 0.0) {
-    if (ry == 1) {
-      if (Rk == 3) go(k_restrict_g<T, 3, true, 0, false, true>); else go(k_restrict_g<T, 6, true, 0, false, true>);
-    } else if (CX == 32 && CY == 4) go(k_restrict_g<T, 3, true, 32>);
+  } else if (relax) {
+    if (CX == 32 && CY == 4) go(k_restrict_g<T, 3, true, 32>);
     else if (Rk == 3) go(k_restrict_g<T, 3, true>);
     else go(k_restrict_g<T, 6, true>);
   } else {
