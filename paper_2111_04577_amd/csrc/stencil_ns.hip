@@ -29,14 +29,17 @@ namespace {
 
 constexpr int kBlock = 256;
 
-template <typename T>
+// The 2D form: one thread per face (too few columns to feed z-marching blocks). With one cell in y
+// as a constant every y neighbour is the cell itself and is loaded once; bound by latency (FP64
+// Oldroyd-B, 128 x 64 cells: 12.5 us with the extent and the polymer as run-time values, 10.8 us so).
+template <typename T, bool VE>
 __global__ void __launch_bounds__(kBlock)
     k_momentum_rhs(NsIn<T> in, Restricted<T> R, T* __restrict__ ru, T* __restrict__ rv,
-                   T* __restrict__ rw, int nx, int ny, int nz, T ihx, T ihy, T ihz, StepConsts c) {
+                   T* __restrict__ rw, int nx, int nz, T ihx, T ihy, T ihz, StepConsts c) {
   int bx, by, bz;
   xcd_tile(bx, by, bz);
   const int i = bx * blockDim.x + threadIdx.x;
-  const int j = by * blockDim.y + threadIdx.y;
+  constexpr int ny = 1, j = 0;
   // blockIdx.z = 3 k + component: the three components of one layer are neighbouring tiles,
   // so each XCD's slab covers all of them and the shared inputs stay in its L2
   const int k = bz / 3;
@@ -56,7 +59,7 @@ __global__ void __launch_bounds__(kBlock)
               {in.taun, in.taunm1, R.phi_c, nx, ny, nz, f},
               R,
               in.un, in.unm1, in.vn, in.vnm1, in.wn, in.wnm1,
-              nx, ny, nz, f, in.viscoelastic,
+              nx, ny, nz, f, VE,
               ihx, ihy, ihz,
               (T)c.inv_dt, (T)c.inv_re, (T)c.inv_rho0, (T)c.nu_m, (T)c.k_sigma, (T)c.c_j};
   const int id = (k * ny + j) * nx + i;
@@ -501,16 +504,17 @@ struct TauOut {
   T* p[6];
 };
 
-// DIV: the WENO-Z face values in the form of weno_face_div (2D grids).
-template <typename T, bool WENO, bool DIV = false>
+// Y3D false: one cell in y, known to the compiler, and the WENO-Z face values of weno_face_div.
+template <typename T, bool WENO, bool Y3D>
 __global__ void __launch_bounds__(kBlock)
     k_polymer_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w,
-                    TauSet<T> tn, TauSet<T> tin, TauOut<T> tout, int nx, int ny, int nz, T ihx,
+                    TauSet<T> tn, TauSet<T> tin, TauOut<T> tout, int nx, int ny_, int nz, T ihx,
                     T ihy, T ihz, T dt, T inv_wi, T one_m_beta, T gk, T c0, T c1, Walls<T> wl) {
+  constexpr bool DIV = !Y3D;  // see weno_face_div
   int bx, by, bz;
   xcd_tile(bx, by, bz);
   const int i = bx * blockDim.x + threadIdx.x;
-  const int j = by * blockDim.y + threadIdx.y;
+  const int ny = Y3D ? ny_ : 1, j = Y3D ? by * blockDim.y + threadIdx.y : 0;
   const int k = bz;
   const int id = (k * ny + j) * nx + i;
   const Coarse<T> U{u, nx, ny, nz}, V{v, nx, ny, nz}, Wf{w, nx, ny, nz};
@@ -857,8 +861,8 @@ hipError_t launch_momentum_rhs(const Dims& c, const StepConsts& k, NsIn<T> in, R
   if (c.ny == 1) {
     // 2D: too few columns to feed z-marching blocks; one thread per face instead
     const Launch3 L = launch3(c.nx, c.ny, 3 * c.nz);
-    hipLaunchKernelGGL(k_momentum_rhs<T>, L.grid, L.block, 0, st, in, r, ru, rv, rw, c.nx, c.ny, c.nz,
-                       (T)c.ihx, (T)c.ihy, (T)c.ihz, k);
+    auto kernel = in.viscoelastic ? k_momentum_rhs<T, true> : k_momentum_rhs<T, false>;
+    hipLaunchKernelGGL(kernel, L.grid, L.block, 0, st, in, r, ru, rv, rw, c.nx, c.nz, (T)c.ihx, (T)c.ihy, (T)c.ihz, k);
     return hipGetLastError();
   }
   // FP32: 64 x 8 columns (512 threads, two blocks per CU) where the grid allows: the halo tile
@@ -926,12 +930,11 @@ hipError_t launch_polymer_stage(const Dims& c, const StepConsts& k, const T* u, 
     hipLaunchKernelGGL(kernel, L.grid, L.block, 0, st, u, v, w, tn, ti, to, c.nx, c.ny, c.nz, (T)c.ihx,
                        (T)c.ihy, (T)c.ihz, (T)k.dt, (T)k.inv_wi, (T)(1.0 - k.beta), gk, (T)c0, (T)c1, wl);
   };
-  if (k.advection != 1)
-    go(k_polymer_stage<T, false>);
-  else if (c.ny == 1)
-    go(k_polymer_stage<T, true, true>);
-  else
-    go(k_polymer_stage<T, true>);
+  if (c.ny == 1) {
+    if (k.advection == 1) go(k_polymer_stage<T, true, false>); else go(k_polymer_stage<T, false, false>);
+  } else {
+    if (k.advection == 1) go(k_polymer_stage<T, true, true>); else go(k_polymer_stage<T, false, true>);
+  }
   return hipGetLastError();
 }
 
