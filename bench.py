@@ -478,7 +478,7 @@ def ingest_pmc(fetch_csv, write_csv, out_json, workload):
     base = {"k_ch_rhs": "ch_rhs", "k_ch_fft": "ch_rhs_fft_x", "k_restrict_g": "restrict_g",
             "k_restrict_g_2d": "restrict_g", "k_momentum_rhs": "momentum_rhs",
             "k_momentum_rhs_zm": "momentum_rhs", "k_polymer_div_zm": "momentum_rhs", "k_polymer_rk2_zm": "polymer_rk2",
-            "k_zpass_ch": "zpass_ch", "k_zpass_ns": "zpass_ns",
+            "k_zpass_ch": "zpass_ch", "k_zpass_ns": "zpass_ns", "k_zpass_ns_scan": "zpass_ns",
             "k_fft_xy_fwd": "fft_xy_fwd_coarse", "k_fft_xy_inv": "fft_xy_inv_coarse"}
     sizes = defaultdict(set)
     for (k, t, inv, g) in fetch:

@@ -705,6 +705,271 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))
   }
 }
 
+// The same projection for 3D grids, by first-order recurrences. In the interior both operators
+// are a (S + S^-1) - (2 a + g), S the shift by a row, g > 0 the gap of the mode, which factor as
+// -(a / rho) (1 - rho S^-1)(1 - rho S) with rho = 2 a / (2 a + g + s), s = sqrt(g (4 a + g)): a forward
+// recurrence z_k = c d_k + rho z_{k-1} (c = -rho / a), a backward one y_k = z_k + rho y_{k+1}, and the
+// wall rows by the homogeneous solutions, x_k = y_k + A rho^k + B rho^(N-1-k). With y_0, y_{N-1} and
+// r = rho^N the walls give
+//   no slip at centres (u, v): A + r B = -rho y_0, B + r A = -rho y_{N-1} / (1 + rho);
+//   faces (w; z_{N-1} = 0): A = -rho^2 y_0 / (1 - r^2), B = -rho^(N-1) A;
+//   zero flux (p'): A - r B = rho y_0, B - r A = rho y_{N-1} / (1 - rho), 1 - rho = (g + s) / (2 a + g + s);
+//   zero flux with g = 0 (the (0,0) mode, whose data sum to zero): A = B = 0, the mean removed after.
+// The gap enters without the cancellation that forming the diagonal brings: against 80-bit
+// elimination the largest error over 16 to 512 rows and g / a from 1e-4 to 1e3 is 1.3e-6 in FP32 (cyclic
+// reduction 1.8e-4) and 2.1e-14 in FP64 (1.7e-12).
+//
+// A thread keeps R consecutive rows of a mode's four fields in registers; recurrences run over its
+// own rows, a few threads then carry the segment ends along the line through LDS (scan), and each
+// thread adds the powers of rho times its carry. Against cyclic reduction (a row per thread, log2(N)
+// steps of two barriers over ten LDS planes, each step also reducing the matrix) the pass does two
+// multiply-adds a value where that did 4 log2(N), and ten barriers where that did 4 log2(N) + 6.
+// 256 x 256 x 128: 145 -> 52 us FP32 (its seven spectral words in and out take 46 at the copy rate);
+// 128 x 128 x 64 FP64: 28.2 -> 15.4 us.
+template <typename T, int R>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+    k_zpass_ns_scan(cx<T>* __restrict__ spec, int P, int Ny, int Nz, int TL, const double* __restrict__ lamx,
+                    const double* __restrict__ lamy, const double* __restrict__ phx,
+                    const double* __restrict__ phy, double ihx, double ihy, double ihz, double nu_m,
+                    double g_dt, double g_rho_dt, double scale, double4 wall) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int S = Nz / R;  // segments of a line
+  const int tid = threadIdx.x, line = tid & (TL - 1), seg = tid / TL;
+  const int ltl = __ffs(TL) - 1;
+  const int lines = P * Ny;
+  const int l0 = xcd_block() * TL, l = l0 + line;
+  const bool valid = l < lines;
+  const int lc = valid ? l : lines - 1;
+  int ky, kx;
+  spec_mode(lc, P, Ny, ky, kx);
+  const size_t stride = (size_t)lines, fsz = stride * Nz;
+  const size_t at0 = (size_t)seg * R * stride + lc;
+  // LDS: segment ends of p' and of u, v, w ([field][segment][line]), the last z of p', u, v, the
+  // wall coefficients A, B, and per line the constants of the scans
+  cx<double>* Ep = reinterpret_cast<cx<double>*>(smem);
+  cx<double>* Yp = Ep + S * TL;
+  cx<double>* Cp = Yp + TL;                                // [A, B][line]
+  double* Kp = reinterpret_cast<double*>(Cp + 2 * TL);     // [4][line]
+  T* Kv = reinterpret_cast<T*>(Kp + 4 * TL);               // [8][line]
+  cx<T>* Ev = reinterpret_cast<cx<T>*>(Kv + 8 * TL);
+  cx<T>* Yv = Ev + 3 * S * TL;                             // [field][line]
+  cx<T>* Cv = Yv + 3 * TL;                                 // [field][A, B][line]
+  cx<T> d[3][R];
+#pragma unroll
+  for (int f = 0; f < 3; ++f)
+#pragma unroll
+    for (int q = 0; q < R; ++q) d[f][q] = spec[f * fsz + at0 + q * stride];
+  const double lxy = lamx[kx] + lamy[ky];
+  const bool bot = seg == 0, top = seg == S - 1;
+  auto ipow = [](auto x, int n) {  // x^n, n < 128
+    auto y = x;
+    y = 1;
+#pragma unroll
+    for (int b = 0; b < 7; ++b) {
+      if (n >> b & 1) y *= x;
+      x *= x;
+    }
+    return y;
+  };
+  // carries of the recurrence with ratio k over the segment ends E (n values of a line's
+  // segments, each component on its own), forward or backward; fin receives the value past the last
+  auto scan = [&](auto* E, const auto* K, int n, bool fwd, auto&& fin) {
+    for (int e = tid; e < 2 * n * TL; e += blockDim.x) {
+      const int f = e >> (ltl + 1), o = e & (2 * TL - 1), t = o >> 1;
+      auto* p = E + (size_t)f * S * 2 * TL + o;
+      const auto k = K[t];
+      auto c = k;
+      c = 0;
+      for (int s = 0; s < S; s += 2) {  // S is even
+        const int s0 = (fwd ? s : S - 1 - s) * 2 * TL, s1 = (fwd ? s + 1 : S - 2 - s) * 2 * TL;
+        const auto e0 = p[s0], e1 = p[s1];
+        p[s0] = c;
+        c = e0 + k * c;
+        p[s1] = c;
+        c = e1 + k * c;
+      }
+      fin(f, t, o & 1, c);
+    }
+  };
+  // ---- velocity Helmholtz (nu_m L - gamma0/dt) u~ = r
+  const double av = nu_m * ihz * ihz;
+  T rho, cf, pw[R];
+  {
+    const double g = g_dt - nu_m * lxy, b = 2.0 * av + g, s = sqrt(g * (b + 2.0 * av));
+    const double rd = 2.0 * av / (b + s);
+    cf = (T)(-2.0 / (b + s));
+    rho = (T)rd;
+    pw[0] = (T)1;
+#pragma unroll
+    for (int q = 1; q < R; ++q) pw[q] = pw[q - 1] * rho;
+    if (bot) {
+      const double rR = ipow(rd, R), rN = ipow(rR, S), i1 = 1.0 / (1.0 - rN * rN), ip = 1.0 / (1.0 + rd);
+      const double kv[8] = {rR, -rd * i1, rN * rd * ip * i1, -rd * ip * i1, rN * rd * i1, -rd * rd * i1,
+                            rd * rN * i1, 0.0};  // rho^2 rho^(N-1) i1
+#pragma unroll
+      for (int q = 0; q < 8; ++q) Kv[q * TL + line] = (T)kv[q];
+    }
+  }
+  const T cs = cf * (T)scale;
+  // moving walls (eq. NS13): -nu_m 2 u_w / hz^2 on the wall rows of the (0,0) mode
+  const T w0 = l == 0 ? (T)1 : (T)0;
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) d[f][q] = cs * d[f][q];
+    if (f < 2) {
+      if (bot) d[f][0].re += w0 * cf * (T)(f == 0 ? wall.x : wall.z);
+      if (top) d[f][R - 1].re += w0 * cf * (T)(f == 0 ? wall.y : wall.w);
+    } else if (top) {
+      d[f][R - 1] = mk<T>(0, 0);
+    }
+#pragma unroll
+    for (int q = 1; q < R; ++q)
+      d[f][q] = mk<T>(d[f][q].re + rho * d[f][q - 1].re, d[f][q].im + rho * d[f][q - 1].im);
+    Ev[(f * S + seg) * TL + line] = d[f][R - 1];
+  }
+  __syncthreads();
+  scan(reinterpret_cast<T*>(Ev), Kv, 3, true,
+       [&](int f, int t, int cc, T c) { reinterpret_cast<T*>(Yv)[(f * TL + t) * 2 + cc] = c; });
+  __syncthreads();
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    const cx<T> c = rho * Ev[(f * S + seg) * TL + line];
+#pragma unroll
+    for (int q = 0; q < R; ++q) d[f][q] = mk<T>(d[f][q].re + pw[q] * c.re, d[f][q].im + pw[q] * c.im);
+    if (f == 2 && top) d[f][R - 1] = mk<T>(0, 0);
+#pragma unroll
+    for (int q = R - 2; q >= 0; --q)
+      d[f][q] = mk<T>(d[f][q].re + rho * d[f][q + 1].re, d[f][q].im + rho * d[f][q + 1].im);
+    Ev[(f * S + seg) * TL + line] = d[f][0];
+  }
+  __syncthreads();
+  scan(reinterpret_cast<T*>(Ev), Kv, 3, false, [&](int f, int t, int cc, T y0) {
+    const T y1 = reinterpret_cast<const T*>(Yv)[(f * TL + t) * 2 + cc];
+    auto K = [&](int q) { return Kv[q * TL + t]; };
+    T* C = reinterpret_cast<T*>(Cv) + f * 4 * TL + 2 * t + cc;
+    C[0] = f < 2 ? K(1) * y0 + K(2) * y1 : K(5) * y0;
+    C[2 * TL] = f < 2 ? K(3) * y1 + K(4) * y0 : K(6) * y0;
+  });
+  __syncthreads();
+  {
+    const T rR = pw[R - 1] * rho, pa = ipow(rR, seg), pb = ipow(rR, S - 1 - seg);
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+      const cx<T> A = pa * Cv[f * 2 * TL + line];
+      const cx<T> B = pb * Cv[f * 2 * TL + TL + line] + rho * Ev[(f * S + seg) * TL + line];
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        d[f][q] = mk<T>(d[f][q].re + pw[q] * A.re + pw[R - 1 - q] * B.re,
+                        d[f][q].im + pw[q] * A.im + pw[R - 1 - q] * B.im);
+    }
+  }
+  if (top) d[2][R - 1] = mk<T>(0, 0);
+  Ev[(2 * S + seg) * TL + line] = d[2][R - 1];
+  __syncthreads();
+  // ---- divergence at centres: D_x = (1 - e^{-i th_x}) / hx, D_z w = (w_k - w_{k-1}) / hz, and the FP64
+  // Poisson equation for p'
+  const double cxr = phx[2 * kx], cxi = phx[2 * kx + 1];
+  const double cyr = phy[2 * ky], cyi = phy[2 * ky + 1];
+  const double ap = ihz * ihz;
+  const bool pinned = kx == 0 && ky == 0;
+  double rp, pwp[R];
+  cx<double> p[R];
+  {
+    const double g = -lxy, b = 2.0 * ap + g, s = sqrt(g * (b + 2.0 * ap));
+    rp = 2.0 * ap / (b + s);
+    const double cp = -2.0 / (b + s);
+    pwp[0] = 1.0;
+#pragma unroll
+    for (int q = 1; q < R; ++q) pwp[q] = pwp[q - 1] * rp;
+    if (bot) {
+      const double rR = ipow(rp, R), rN = ipow(rR, S);
+      const double i1 = pinned ? 0.0 : 1.0 / (1.0 - rN * rN);
+      Kp[line] = rR;
+      Kp[TL + line] = rN;
+      Kp[2 * TL + line] = rp * i1;
+      Kp[3 * TL + line] = pinned ? 0.0 : rp * (b + s) / (g + s) * i1;
+    }
+    const double m = g_rho_dt * cp;
+    const double dxr = m * (1.0 - cxr) * ihx, dxi = m * cxi * ihx;
+    const double dyr = m * (1.0 - cyr) * ihy, dyi = m * cyi * ihy, dz = m * ihz;
+    cx<double> wm = bot ? mk<double>(0, 0) : widen<double>(Ev[(2 * S + seg - 1) * TL + line]);
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const cx<double> u = widen<double>(d[0][q]), v = widen<double>(d[1][q]), w = widen<double>(d[2][q]);
+      p[q] = mk<double>(dxr * u.re - dxi * u.im + dyr * v.re - dyi * v.im + (w.re - wm.re) * dz,
+                        dxr * u.im + dxi * u.re + dyr * v.im + dyi * v.re + (w.im - wm.im) * dz);
+      wm = w;
+      if (q > 0) p[q] = mk<double>(p[q].re + rp * p[q - 1].re, p[q].im + rp * p[q - 1].im);
+    }
+  }
+  Ep[seg * TL + line] = p[R - 1];
+  __syncthreads();
+  scan(reinterpret_cast<double*>(Ep), Kp, 1, true,
+       [&](int, int t, int cc, double c) { reinterpret_cast<double*>(Yp)[2 * t + cc] = c; });
+  __syncthreads();
+  {
+    const cx<double> c = rp * Ep[seg * TL + line];
+#pragma unroll
+    for (int q = 0; q < R; ++q) p[q] = mk<double>(p[q].re + pwp[q] * c.re, p[q].im + pwp[q] * c.im);
+#pragma unroll
+    for (int q = R - 2; q >= 0; --q) p[q] = mk<double>(p[q].re + rp * p[q + 1].re, p[q].im + rp * p[q + 1].im);
+    Ep[seg * TL + line] = p[0];
+  }
+  __syncthreads();
+  scan(reinterpret_cast<double*>(Ep), Kp, 1, false, [&](int, int t, int cc, double y0) {
+    const double y1 = reinterpret_cast<const double*>(Yp)[2 * t + cc];
+    const double rN = Kp[TL + t], e = Kp[2 * TL + t] * y0, f = Kp[3 * TL + t] * y1;
+    double* C = reinterpret_cast<double*>(Cp) + 2 * t + cc;
+    C[0] = e + rN * f;
+    C[2 * TL] = f + rN * e;
+  });
+  __syncthreads();
+  {
+    const double rR = pwp[R - 1] * rp;
+    const cx<double> A = ipow(rR, seg) * Cp[line];
+    const cx<double> B = ipow(rR, S - 1 - seg) * Cp[TL + line] + rp * Ep[seg * TL + line];
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      p[q] = mk<double>(p[q].re + pwp[q] * A.re + pwp[R - 1 - q] * B.re,
+                        p[q].im + pwp[q] * A.im + pwp[R - 1 - q] * B.im);
+  }
+  if (l0 == 0) {  // the block of the (0,0) mode: remove its mean
+    cx<double> m = mk<double>(0, 0);
+#pragma unroll
+    for (int q = 0; q < R; ++q) m = m + p[q];
+    Ep[seg * TL + line] = m;
+    __syncthreads();
+    if (pinned) {
+      m = mk<double>(0, 0);
+      for (int s = 0; s < S; ++s) m = m + Ep[s * TL + line];
+#pragma unroll
+      for (int q = 0; q < R; ++q) p[q] = mk<double>(p[q].re - m.re / Nz, p[q].im - m.im / Nz);
+    }
+    __syncthreads();
+  }
+  Ep[seg * TL + line] = p[0];
+  __syncthreads();
+  // ---- correction u = u~ - c grad p', G_x = (e^{i th_x} - 1) / hx
+  if (!valid) return;
+  const double cg = 1.0 / g_rho_dt;
+  const double gxr = cg * (cxr - 1.0) * ihx, gxi = cg * cxi * ihx;
+  const double gyr = cg * (cyr - 1.0) * ihy, gyi = cg * cyi * ihy, gz = cg * ihz;
+  const cx<double> pn = top ? mk<double>(0, 0) : Ep[(seg + 1) * TL + line];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const size_t at = at0 + q * stride;
+    const cx<double> u = widen<double>(d[0][q]), v = widen<double>(d[1][q]), w = widen<double>(d[2][q]);
+    const double pr = p[q].re, pi = p[q].im;
+    const cx<double> up = q + 1 < R ? p[(q + 1) % R] : pn;
+    spec[at] = mk<T>((T)(u.re - (gxr * pr - gxi * pi)), (T)(u.im - (gxr * pi + gxi * pr)));
+    spec[fsz + at] = mk<T>((T)(v.re - (gyr * pr - gyi * pi)), (T)(v.im - (gyr * pi + gyi * pr)));
+    spec[2 * fsz + at] = top && q == R - 1 ? mk<T>(0, 0)
+                                           : mk<T>((T)(w.re - (up.re - pr) * gz), (T)(w.im - (up.im - pi) * gz));
+    spec[3 * fsz + at] = mk<T>((T)pr, (T)pi);
+  }
+}
+
 // ---- Navier-Stokes projection, transposed (FP64) --------------------------------------
 // With Pi = I - G P+ D the projection (P+ the pseudo-inverse of the Neumann Laplacian, whose
 // transpose is itself; G^T = -D with the top-wall w held at zero) and p^{n+1} = p^n + k P+ D u~
@@ -937,6 +1202,31 @@ template <typename T>
 hipError_t launch_zpass_ns(const Dims& d, const Tables<T>& tb, cx<T>* spec4, const StepConsts& c,
                            double scale, hipStream_t st) {
   const int lines = d.lines();
+  const double bw = -2.0 * c.nu_m / (d.hz * d.hz);
+  const double4 wall = make_double4(bw * c.uwb[0], bw * c.uwt[0], bw * c.uwb[1], bw * c.uwt[1]);
+  // Recurrences where columns are deep or many; cyclic reduction, whose row per thread makes more
+  // wavefronts of a small grid, where they are neither, and in 2D (a viscoelastic 2D run carries a
+  // normal velocity that is round-off: its results stay bitwise what they were). Us per step,
+  // reduction against recurrences: 32 x 32 x 16 FP32 78.3, 80.9; 128 x 128 x 16 FP64 159.5, 160.6;
+  // 32 x 32 x 64 FP64 76.1, 77.7; 64 x 64 x 32 FP64 99.1, 99.5; 128 x 64 x 32 109.1, 107.8 FP32 and
+  // 146.1, 144.6 FP64; 64 x 64 x 64 108.3, 105.7 and 143.0, 140.3; 16 x 32 x 128 81.4, 79.1 and 91.5,
+  // 90.8; 256 x 256 x 128 1994, 1903 and 3668, 3553. Rows per thread: 8, and 4 for 32 rows (128 x 64 x 32
+  // FP32 108.9 with 8, 107.8 with 4; 256 x 256 x 128 1903 with 8, 1908 with 4).
+  if (d.ny > 1 && (d.nz >= 128 || (d.nz >= 32 && lines * d.nz >= 1 << 17))) {
+    auto go = [&](auto kernel, int R) {
+      const int S = d.nz / R;
+      // 128 bytes of a row per block, at most 256 threads
+      int TL = (int)(128 / sizeof(cx<T>));
+      while (TL > 1 && TL * S > 256) TL >>= 1;
+      const size_t shm = (size_t)TL * ((S + 3) * sizeof(cx<double>) + 4 * sizeof(double) + 8 * sizeof(T) +
+                                       (3 * S + 9) * sizeof(cx<T>));
+      hipLaunchKernelGGL(kernel, dim3((lines + TL - 1) / TL), dim3(TL * S), shm, st, spec4, d.pitch, d.ny, d.nz, TL,
+                         tb.lam_x, tb.lam_y, tb.ph_x, tb.ph_y, 1.0 / d.hx, 1.0 / d.hy, 1.0 / d.hz, c.nu_m,
+                         c.gamma0 / c.dt, c.gamma0 * c.rho0 / c.dt, scale, wall);
+    };
+    if (d.nz >= 64) go(k_zpass_ns_scan<T, 8>, 8); else go(k_zpass_ns_scan<T, 4>, 4);
+    return hipGetLastError();
+  }
   auto shm_of = [&](int tl) {
     const size_t a = pcr_sym_bytes<T, 2, 3>(d.nz, tl), b = pcr_sym_bytes<double, 1, 1>(d.nz, tl);
     return a > b ? a : b;
@@ -945,8 +1235,6 @@ hipError_t launch_zpass_ns(const Dims& d, const Tables<T>& tb, cx<T>* spec4, con
   int TL = tile_lines(d.nz);
   while (TL > 1 && shm_of(TL) > 65536) TL >>= 1;
   TL = spread_lines(TL, lines, 2048, d.nz);
-  const double bw = -2.0 * c.nu_m / (d.hz * d.hz);
-  const double4 wall = make_double4(bw * c.uwb[0], bw * c.uwt[0], bw * c.uwb[1], bw * c.uwt[1]);
   // FP32: registers for two blocks of 1024 threads per CU; FP64 (whose LDS allows one such
   // block) unconstrained
   constexpr int WPE = sizeof(T) == 4 ? 8 : 4;
