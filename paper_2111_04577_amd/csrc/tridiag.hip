@@ -716,16 +716,16 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))
 //   zero flux (p'): A - r B = rho y_0, B - r A = rho y_{N-1} / (1 - rho), 1 - rho = (g + s) / (2 a + g + s);
 //   zero flux with g = 0 (the (0,0) mode, whose data sum to zero): A = B = 0, the mean removed after.
 // The gap enters without the cancellation that forming the diagonal brings: against 80-bit
-// elimination the largest error over 16 to 512 rows and g / a from 1e-4 to 1e3 is 1.3e-6 in FP32 (cyclic
-// reduction 1.8e-4) and 2.1e-14 in FP64 (1.7e-12).
+// elimination the largest error over 16 to 512 rows and g / a from 1e-4 to 1e3 is 2.1e-14 (cyclic reduction
+// 1.7e-12).
 //
 // A thread keeps R consecutive rows of a mode's four fields in registers; recurrences run over its
 // own rows, a few threads then carry the segment ends along the line through LDS (scan), and each
 // thread adds the powers of rho times its carry. Against cyclic reduction (a row per thread, log2(N)
 // steps of two barriers over ten LDS planes, each step also reducing the matrix) the pass does two
 // multiply-adds a value where that did 4 log2(N), and ten barriers where that did 4 log2(N) + 6.
-// 256 x 256 x 128: 145 -> 52 us FP32 (its seven spectral words in and out take 46 at the copy rate);
-// 128 x 128 x 64 FP64: 28.2 -> 15.4 us.
+// FP64, 256 x 256 x 128: 217 -> 105 us (its seven spectral words in and out take 92 at the copy rate);
+// 128 x 128 x 64: 28.2 -> 15.4 us.
 template <typename T, int R>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
     k_zpass_ns_scan(cx<T>* __restrict__ spec, int P, int Ny, int Nz, int TL, const double* __restrict__ lamx,
@@ -1204,15 +1204,17 @@ hipError_t launch_zpass_ns(const Dims& d, const Tables<T>& tb, cx<T>* spec4, con
   const int lines = d.lines();
   const double bw = -2.0 * c.nu_m / (d.hz * d.hz);
   const double4 wall = make_double4(bw * c.uwb[0], bw * c.uwt[0], bw * c.uwb[1], bw * c.uwt[1]);
-  // Recurrences where columns are deep or many; cyclic reduction, whose row per thread makes more
-  // wavefronts of a small grid, where they are neither, and in 2D (a viscoelastic 2D run carries a
-  // normal velocity that is round-off: its results stay bitwise what they were). Us per step,
-  // reduction against recurrences: 32 x 32 x 16 FP32 78.3, 80.9; 128 x 128 x 16 FP64 159.5, 160.6;
-  // 32 x 32 x 64 FP64 76.1, 77.7; 64 x 64 x 32 FP64 99.1, 99.5; 128 x 64 x 32 109.1, 107.8 FP32 and
-  // 146.1, 144.6 FP64; 64 x 64 x 64 108.3, 105.7 and 143.0, 140.3; 16 x 32 x 128 81.4, 79.1 and 91.5,
-  // 90.8; 256 x 256 x 128 1994, 1903 and 3668, 3553. Rows per thread: 8, and 4 for 32 rows (128 x 64 x 32
-  // FP32 108.9 with 8, 107.8 with 4; 256 x 256 x 128 1903 with 8, 1908 with 4).
-  if (d.ny > 1 && (d.nz >= 128 || (d.nz >= 32 && lines * d.nz >= 1 << 17))) {
+  // FP64 grids: recurrences where columns are deep or many; cyclic reduction, whose row per thread
+  // makes more wavefronts of a small grid, where they are neither, and in 2D (a viscoelastic 2D run
+  // carries a normal velocity that is round-off: its results stay bitwise what they were). FP32
+  // keeps the reduction: where the pressure gradient all but cancels u~ (a flow starting from rest on
+  // a 256 x 16 x 128 single-resolution grid), u is 1e-3 of it and u~'s FP32 round-off alone is 7e-5
+  // of u by either method, so that the two differ by as much. Us per step, reduction against
+  // recurrences: 128 x 128 x 16 159.5, 160.6; 32 x 32 x 64 76.1, 77.7; 64 x 64 x 32 99.1, 99.5;
+  // 128 x 64 x 32 146.1, 144.6; 64 x 64 x 64 143.0, 140.3; 16 x 32 x 128 91.5, 90.8;
+  // 256 x 256 x 128 3668, 3553. Rows per thread: 8, and 4 for 32 rows (128 x 64 x 32 145.8 with
+  // 8, 144.6 with 4; 256 x 256 x 128 3553 with 8, 3558 with 4).
+  if constexpr (sizeof(T) == 8) if (d.ny > 1 && (d.nz >= 128 || (d.nz >= 32 && lines * d.nz >= 1 << 17))) {
     auto go = [&](auto kernel, int R) {
       const int S = d.nz / R;
       // 128 bytes of a row per block, at most 256 threads

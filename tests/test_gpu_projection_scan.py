@@ -1,8 +1,8 @@
-"""GPU parity of the wall-normal projection by recurrences (3D, deep or many columns) at the edges of
+"""GPU parity of the wall-normal projection by recurrences (3D FP64, deep or many columns) at the edges of
 its range: the shallowest columns it takes, one to 16 modes per block, a last block that is not
 full, the deepest columns, moving walls, a single resolution. One phase at rest, a rough velocity:
 one step against the FP64 oracle, FP64 1e-10 of the largest velocity (round-off of a stiff solve);
-FP32 2e-5 (storage and transform round-off of a velocity of order one, 1e-6, and of the pressure
+FP32 (cyclic reduction) 2e-5 (storage and transform round-off of a velocity of order one, 1e-6, and of the pressure
 gradient that the rough velocity's divergence needs, some ten times that)."""
 from __future__ import annotations
 
