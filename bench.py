@@ -104,9 +104,9 @@ def alg_bytes(kernel, cfg, es):
         "zpass_ch": 2 * sf,
         "fft_y_inv_fine": 2 * sf if F["ny"] > 1 else 0,
         "fft_x_inv_fine": sf + nf,
-        # single resolution: G and phi at the cells (2 N_c written), then faces and edges from
-        # them (2 N_c read back) in a second kernel, both under this timing id
-        "restrict_g": 3 * nf + (12 if cfg.refine == 1 else 10) * nc + 2 * ne,
+        # single resolution in 2D: G and phi at the cells (2 N_c written), then faces and edges
+        # from them (2 N_c read back) in a second kernel, both under this timing id
+        "restrict_g": 3 * nf + (12 if cfg.refine == 1 and C["ny"] == 1 else 10) * nc + 2 * ne,
         "momentum_rhs": (8 + 10 + 12 * ve + 3) * nc + 2 * ne,
         "fft_x_fwd_coarse": 3 * nc + 3 * sc,
         "fft_y_fwd_coarse": 6 * sc if C["ny"] > 1 else 0,
@@ -476,7 +476,7 @@ def ingest_pmc(fetch_csv, write_csv, out_json, workload):
     # the polymer divergence pass is timed with the momentum kernel (one profiling id): its bytes
     # are added to momentum_rhs's
     base = {"k_ch_rhs": "ch_rhs", "k_ch_fft": "ch_rhs_fft_x", "k_restrict_g": "restrict_g",
-            "k_restrict_g_2d": "restrict_g", "k_momentum_rhs": "momentum_rhs",
+            "k_restrict_g_2d": "restrict_g", "k_props_single_zm": "restrict_g", "k_momentum_rhs": "momentum_rhs",
             "k_momentum_rhs_zm": "momentum_rhs", "k_polymer_div_zm": "momentum_rhs", "k_polymer_rk2_zm": "polymer_rk2",
             "k_zpass_ch": "zpass_ch", "k_zpass_ns": "zpass_ns", "k_zpass_ns_scan": "zpass_ns",
             "k_fft_xy_fwd": "fft_xy_fwd_coarse", "k_fft_xy_inv": "fft_xy_inv_coarse"}

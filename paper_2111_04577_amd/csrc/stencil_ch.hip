@@ -827,6 +827,136 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
+// Both in one z-march for 3D grids but with moving relaxed walls: a block owns TX x TY columns and KB
+// layers. phi^{n+1} of four layers (one cell of halo below, two above in x and y) and G of two layers
+// (one cell above) live in LDS; a step brings in one phi layer and evaluates G once on one layer, then
+// each thread forms its cell's restricted set from them, so neither G nor phi_c is read back and no
+// neighbour is read from memory twice (15 words a cell instead of 17 plus re-read halos). The next
+// layers' loads are in flight meanwhile. FP32, 256 x 256 x 128: 49 + 115 us as two passes of a thread
+// per cell, 112 us so (98 at the copy rate). 2D grids, whose few columns would make few blocks, keep
+// the two passes.
+template <typename T, int R, bool RELAX>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+    k_props_single_zm(const T* __restrict__ phinew, const T* __restrict__ phin, const T* __restrict__ phinm1,
+                      Restricted<T> r, int nx, int ny, int nz, int KB, T ihx, T ihy, T ihz, StepConsts c) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int TX = blockDim.x, TY = blockDim.y;
+  int bx, by, bz;
+  xcd_tile(bx, by, bz);
+  const int X0 = bx * TX, Y0 = by * TY, k0 = bz * KB, k1 = min(k0 + KB, nz);
+  const int PX = TX + 3, PP = PX * (TY + 3), GX = TX + 1, GP = GX * (TY + 1);
+  T* sP = reinterpret_cast<T*>(smem);  // layer K in slot K & 3
+  T* sG = sP + 4 * PP;                 // layer K in slot K & 1
+  const int tx = threadIdx.x, ty = threadIdx.y, nth = TX * TY, tid = ty * TX + tx;
+  const bool first = c.first != 0;
+  const size_t layer = (size_t)ny * nx;
+  auto kc = [&](int K) { return min(max(K, 0), nz - 1); };
+  unsigned pOff[R], gOff[R];
+  int gM[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int e = tid + q * nth;
+    const int py = e / PX, px = e - py * PX, gy = e / GX, gx = e - gy * GX;
+    pOff[q] = e < PP ? (unsigned)(wrap(Y0 - 1 + py, ny) * nx + wrap(X0 - 1 + px, nx)) * sizeof(T) : 0u;
+    gOff[q] = e < GP ? (unsigned)(wrap(Y0 + gy, ny) * nx + wrap(X0 + gx, nx)) * sizeof(T) : 0u;
+    gM[q] = e < GP ? (gy + 1) * PX + gx + 1 : PX + 1;
+  }
+  auto load_p = [&](int K, T* v) {
+    const T* a = phinew + kc(K) * layer;
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[q] = ld_at(a, pOff[q]);
+  };
+  auto store_p = [&](int K, const T* v) {
+    T* dst = sP + (K & 3) * PP;
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (tid + q * nth < PP) dst[tid + q * nth] = v[q];
+  };
+  // phi^n and phi^{n-1} at the G points
+  auto load_n = [&](int K, T* a, T* b) {
+    const T *x = phin + kc(K) * layer, *y = phinm1 + kc(K) * layer;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      a[q] = ld_at(x, gOff[q]);
+      b[q] = ld_at(y, gOff[q]);
+    }
+  };
+  const T ihx2 = ihx * ihx, ihy2 = ihy * ihy, ihz2 = ihz * ihz, cn2 = (T)c.cn2, S = (T)c.S;
+  auto compute_g = [&](int K, const T* a, const T* bm) {
+    const T *Pm = sP + ((K - 1) & 3) * PP, *P0 = sP + (K & 3) * PP, *Pp = sP + ((K + 1) & 3) * PP;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int m = gM[q];
+      const T p = P0[m];
+      const T lap = (P0[m + 1] - 2 * p + P0[m - 1]) * ihx2 + (P0[m + PX] - 2 * p + P0[m - PX]) * ihy2 +
+                    (Pp[m] - 2 * p + Pm[m]) * ihz2;
+      const T ps = first ? a[q] : (T)2 * a[q] - bm[q];
+      T b = 0;
+      if (K == 0 || K == nz - 1) {
+        b = (T)(K == 0 ? c.g_bot : c.g_top) * ihz * ((T)1 - ps * ps);
+        if (RELAX) {  // (kappa / hz)(phi_hat / gamma0 - phi^{n+1}) in the wall ghost
+          const T ph = first ? a[q] : (T)2 * a[q] - (T)0.5 * bm[q];
+          b += (T)(c.relax_kappa * c.inv_gamma0) * ihz * ph - (T)c.relax_kappa * ihz * p;
+        }
+      }
+      if (tid + q * nth < GP) sG[(K & 1) * GP + tid + q * nth] = -cn2 * (lap + b) + S * (p - ps) + ps * ps * ps - ps;
+    }
+  };
+  T pf[R], na[R], nb[R];
+  {
+    T p1[R], p2[R], p3[R];
+    load_p(k0 - 1, pf);
+    load_p(k0, p1);
+    load_p(k0 + 1, p2);
+    load_p(k0 + 2, p3);
+    load_n(k0, na, nb);
+    store_p(k0 - 1, pf);
+    store_p(k0, p1);
+    store_p(k0 + 1, p2);
+    store_p(k0 + 2, p3);
+  }
+  __syncthreads();
+  compute_g(k0, na, nb);
+  load_p(k0 + 3, pf);
+  load_n(k0 + 1, na, nb);
+  const T h = (T)0.5, r1 = (T)c.rho1, r2 = (T)c.rho2, m1 = (T)c.mu1, m2 = (T)c.mu2;
+  auto rinv = [&](T ph) { return (T)1 / (h * ((T)1 + ph) * r1 + h * ((T)1 - ph) * r2); };
+  auto mu = [&](T ph) { return h * ((T)1 + ph) * m1 + h * ((T)1 - ph) * m2; };
+  const int me = (ty + 1) * PX + tx + 1, mg = ty * GX + tx;
+  for (int k = k0; k < k1; ++k) {
+    __syncthreads();
+    if (k + 1 < nz) compute_g(k + 1, na, nb);
+    store_p(k + 3, pf);  // the slot of layer k - 1, no longer read
+    if (k + 1 < k1) {
+      load_p(k + 4, pf);
+      load_n(k + 2, na, nb);
+    }
+    __syncthreads();
+    const T *P = sP + (k & 3) * PP + me, *U = sP + ((k + 1) & 3) * PP + me;
+    const T* G = sG + (k & 1) * GP + mg;
+    const T g0 = G[0], gu = k + 1 < nz ? sG[((k + 1) & 1) * GP + mg] : g0;
+    const T p0 = P[0], px = P[1], py = P[PX], pxy = P[PX + 1], u0 = U[0], ux = U[1], uy = U[PX];
+    const size_t id = k * layer + (size_t)(Y0 + ty) * nx + X0 + tx;
+    r.G_c[id] = g0;
+    r.phi_c[id] = p0;
+    r.G_x[id] = h * (g0 + G[1]);
+    r.G_y[id] = h * (g0 + G[GX]);
+    r.G_z[id] = h * (g0 + gu);
+    r.ri_x[id] = rinv(h * (p0 + px));
+    r.ri_y[id] = rinv(h * (p0 + py));
+    r.ri_z[id] = rinv(h * (p0 + u0));
+    r.mu_c[id] = mu(p0);
+    r.mu_xy[id] = mu(h * (h * (p0 + px) + h * (py + pxy)));
+    // z-edge arrays carry nz + 1 layers: layer m is the edge at z = m hz
+    r.mu_xz[id + layer] = mu(h * (h * (p0 + px) + h * (u0 + ux)));
+    r.mu_yz[id + layer] = mu(h * (h * (p0 + py) + h * (u0 + uy)));
+    if (k == 0) {
+      r.mu_xz[id] = mu(h * (h * (p0 + px) + h * (p0 + px)));
+      r.mu_yz[id] = mu(h * (h * (p0 + py) + h * (p0 + py)));
+    }
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
     k_prolong(T* __restrict__ uf, T* __restrict__ vf, T* __restrict__ wf, int fnx, int fny,
@@ -1020,6 +1150,27 @@ hipError_t launch_weno_adv_fine(const Dims& f, const Dims& c, const StepConsts& 
 template <typename T>
 hipError_t launch_props_single(const Dims& c, const StepConsts& k, const T* phinew, const T* phin,
                                const T* phinm1, Restricted<T> r, hipStream_t st) {
+  const bool moving = k.uwb[0] != 0.0 || k.uwb[1] != 0.0 || k.uwt[0] != 0.0 || k.uwt[1] != 0.0;
+  const bool relax = k.relax_kappa != 0.0;
+  // 3D but for moving relaxed walls, whose wall term reads phi* around the wall cells
+  if (c.ny > 1 && !(relax && moving)) {
+    const int TX = c.nx < 64 ? c.nx : 64, TY = c.ny < 8 ? c.ny : 8, nth = TX * TY;
+    const int PP = (TX + 3) * (TY + 3), GP = (TX + 1) * (TY + 1);
+    const size_t shm = (size_t)(4 * PP + 2 * GP) * sizeof(T);
+    const int cols = (c.nx / TX) * (c.ny / TY);
+    auto go = [&](auto kernel) {
+      const int KB = march_layers(kernel, nth, shm, cols, c.nz);
+      hipLaunchKernelGGL(kernel, dim3(c.nx / TX, c.ny / TY, (c.nz + KB - 1) / KB), dim3(TX, TY), shm, st, phinew,
+                         phin, phinm1, r, c.nx, c.ny, c.nz, KB, (T)c.ihx, (T)c.ihy, (T)c.ihz, k);
+    };
+    // tile points per thread: 2 for tiles of 32 x 8 and up, 4 for the smallest (4 x 4: 49 of 16)
+    if (PP <= 2 * nth) {
+      if (relax) go(k_props_single_zm<T, 2, true>); else go(k_props_single_zm<T, 2, false>);
+    } else {
+      if (relax) go(k_props_single_zm<T, 4, true>); else go(k_props_single_zm<T, 4, false>);
+    }
+    return hipGetLastError();
+  }
   const Launch3 L = launch3(c.nx, c.ny, c.nz);
   hipLaunchKernelGGL(k_g_single<T>, L.grid, L.block, 0, st, phinew, phin, phinm1, r, c.nx, c.ny, c.nz,
                      (T)c.ihx, (T)c.ihy, (T)c.ihz, k);

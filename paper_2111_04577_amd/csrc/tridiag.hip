@@ -724,7 +724,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))
 // thread adds the powers of rho times its carry. Against cyclic reduction (a row per thread, log2(N)
 // steps of two barriers over ten LDS planes, each step also reducing the matrix) the pass does two
 // multiply-adds a value where that did 4 log2(N), and ten barriers where that did 4 log2(N) + 6.
-// FP64, 256 x 256 x 128: 217 -> 105 us (its seven spectral words in and out take 92 at the copy rate);
+// FP64, 256 x 256 x 128: 217 -> 98 us (its seven spectral words in and out take 92 at the copy rate);
 // 128 x 128 x 64: 28.2 -> 15.4 us.
 template <typename T, int R>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
