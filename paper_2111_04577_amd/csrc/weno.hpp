@@ -10,20 +10,24 @@
 namespace drpf {
 
 // Value at the face between v0 and vp1, reconstructed from the side of v0. Bound by arithmetic:
-// everything that a division can be spared is (the sixths of the candidates, the tenths of d and
-// the quarters of beta scale out of the quotient; eps scales with beta). FP32 divides through the
-// hardware reciprocal, once per candidate and once for the quotient. FP64 multiplies numerator
-// and denominator by the product of the three beta + eps, which leaves one division of seven
-// (the products stay in range: beta + eps >= 4e-40, and <= 1e60 for values up to 1e30). With
-// seven IEEE divisions in FP64 and three (the sixths) beside four reciprocals in FP32, a step of
-// 128 x 128 x 64 coarse cells with WENO-Z took 681 instead of 639 us FP64, 375 instead of 355 us
-// FP32 (Newtonian), and 772 instead of 698 us with the log-conformation update.
+// everything that a division can be spared is (the sixths of the candidates and the quarters of beta
+// scale out of the quotient; eps scales with beta). FP32 divides through the hardware reciprocal,
+// once per candidate and once for the quotient, with d_1 scaled to one and the candidates to 6/16
+// (an exact scale), so that numerator and denominator are as large as with a division each: where
+// the stencil of a candidate is flat (value V) beside a jump d, the numerator reaches 0.5 V d^2 / eps
+// and the ratio 8 d^2 / eps, in range for V d^2 < 4e8, d < 6e3. FP64 multiplies numerator and
+// denominator by the product of the three beta + eps, which leaves one division of seven (in range
+// for values of 1e-189 to 5e42: 4 beta <= 133 v^2, 4 (beta + eps) >= 4e-40). With seven IEEE divisions
+// in FP64 and three (the sixths) beside four reciprocals in FP32, a step of 128 x 128 x 64 coarse
+// cells with WENO-Z took 681 instead of 639 us FP64, 375 instead of 355 us FP32 (Newtonian), and
+// 772 instead of 698 us with the log-conformation update.
 template <typename T>
 __device__ __forceinline__ T weno_face(T vm2, T vm1, T v0, T vp1, T vp2) {
   const T eps = sizeof(T) == 8 ? (T)4e-40 : (T)4e-30;
-  const T q0 = (T)2 * vm2 - (T)7 * vm1 + (T)11 * v0;  // 6 x the candidates
-  const T q1 = (T)5 * v0 + (T)2 * vp1 - vm1;
-  const T q2 = (T)2 * v0 + (T)5 * vp1 - vp2;
+  const T qs = sizeof(T) == 8 ? (T)1 : (T)0.0625;  // 6 qs x the candidates
+  const T q0 = (T)2 * qs * vm2 - (T)7 * qs * vm1 + (T)11 * qs * v0;
+  const T q1 = (T)5 * qs * v0 + (T)2 * qs * vp1 - qs * vm1;
+  const T q2 = (T)2 * qs * v0 + (T)5 * qs * vp1 - qs * vp2;
   const T c13 = (T)(13.0 / 3.0);
   const T s0 = vm2 - (T)2 * vm1 + v0, r0 = vm2 - (T)4 * vm1 + (T)3 * v0;
   const T s1 = vm1 - (T)2 * v0 + vp1, r1 = vm1 - vp1;
@@ -33,17 +37,18 @@ __device__ __forceinline__ T weno_face(T vm2, T vm1, T v0, T vp1, T vp2) {
   const T b2 = c13 * s2 * s2 + r2 * r2;
   const T t5 = fabs(b0 - b2);
   const T e0 = b0 + eps, e1 = b1 + eps, e2 = b2 + eps;
-  T a0, a1, a2;  // 10 x the weights, up to a common factor
+  T a0, a1, a2;  // the weights, up to a common factor
   if constexpr (sizeof(T) == 8) {
     a0 = (e0 + t5) * (e1 * e2);
     a1 = (T)6 * (e1 + t5) * (e0 * e2);
     a2 = (T)3 * (e2 + t5) * (e0 * e1);
     return (a0 * q0 + a1 * q1 + a2 * q2) / ((T)6 * (a0 + a1 + a2));
   } else {
-    a0 = (T)1 + t5 * __builtin_amdgcn_rcpf(e0);
-    a1 = (T)6 + (T)6 * t5 * __builtin_amdgcn_rcpf(e1);
-    a2 = (T)3 + (T)3 * t5 * __builtin_amdgcn_rcpf(e2);
-    return (a0 * q0 + a1 * q1 + a2 * q2) * __builtin_amdgcn_rcpf((T)6 * (a0 + a1 + a2));
+    const T d0 = (T)(1.0 / 6.0), d2 = (T)0.5;
+    a0 = fma(d0 * t5, __builtin_amdgcn_rcpf(e0), d0);
+    a1 = fma(t5, __builtin_amdgcn_rcpf(e1), (T)1);
+    a2 = fma(d2 * t5, __builtin_amdgcn_rcpf(e2), d2);
+    return (a0 * q0 + a1 * q1 + a2 * q2) * __builtin_amdgcn_rcpf((T)6 * qs * (a0 + a1 + a2));
   }
 }
 
