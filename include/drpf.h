@@ -249,9 +249,9 @@ int drpf_prolong(drpf_grid* g, const void* u, const void* v, const void* w, void
 int drpf_restrict(drpf_grid* g, const void* fine, void* coarse, int location, void* stream);
 
 /* Solves coeff * L x - shift * x = rhs on the fine or coarse grid with the 7-point
- * second-order Laplacian L (periodic x, y; boundary kind `bc` in z) by FFT in x and y and
- * a batched tridiagonal solve per Fourier mode across the walls (the "FFT solver" of
- * Sec. 3.2.1-3.2.2). coeff > 0, shift >= 0; shift == 0 is allowed only with
+ * second-order Laplacian L (periodic x, y; boundary kind `bc` in z) by FFT in x and y and,
+ * per Fourier mode across the walls, a cosine or sine transform (NEUMANN, DIRICHLET) or a
+ * tridiagonal solve (FACE_DIRICHLET): the "FFT solver" of Sec. 3.2.1-3.2.2. coeff > 0, shift >= 0; shift == 0 is allowed only with
  * DRPF_BC_NEUMANN and returns the pseudo-inverse's solution: the z-mean of the right-hand
  * side's (0,0) Fourier mode is dropped and the result has zero mean.
  * wall_data: null for homogeneous walls, else a device array of 2 * nx * ny elements of the
@@ -260,8 +260,8 @@ int drpf_restrict(drpf_grid* g, const void* fine, void* coarse, int location, vo
  *     data of eq. NS34 has this form),
  *   DRPF_BC_DIRICHLET: the wall value (ghost = 2 value - adjacent; u = u_w of eq. NS13),
  *   DRPF_BC_FACE_DIRICHLET: the value of the face field on the wall itself.
- * The known wall terms move to the right-hand side (the workspace's spectral buffers and
- * right-hand-side buffer are overwritten). For DRPF_BC_FACE_DIRICHLET layer nz-1 of rhs is
+ * The known wall terms move to the right-hand side as it is read; the workspace's spectral
+ * buffer of the grid is overwritten. For DRPF_BC_FACE_DIRICHLET layer nz-1 of rhs is
  * ignored and that layer of x is set to the top wall's value (0 without wall data). rhs and
  * x may alias; wall_data must not overlap x. */
 int drpf_helmholtz_solve(drpf_grid* g, int which_grid, int bc, double coeff, double shift,
@@ -269,14 +269,12 @@ int drpf_helmholtz_solve(drpf_grid* g, int which_grid, int bc, double coeff, dou
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): drpf_helmholtz_solve with the same arguments,
- * kernels and results, whose scratch (the spectral buffer, and with wall_data the right-hand
- * side with the wall terms) is a static 32 MiB device array of the library instead of the
- * grid's workspace, so that the grid's workspace is left untouched. It calls no hipMalloc,
- * hipFree or allocating routine. DRPF_EWORKSPACE if the solve needs more than 32 MiB of
- * scratch: ((nx/2 + 1) * ny * nz complex elements of the chosen grid, plus nx * ny * nz
- * elements with wall data, the first rounded up to 256 bytes). Every call on one GPU uses that
- * GPU's one array: calls that overlap on a GPU (on different streams, or from several threads)
- * race and must be serialised by the caller. */
+ * kernels and results, whose scratch (the spectral buffer) is a static 32 MiB device array of
+ * the library instead of the grid's workspace, so that the grid's workspace is left untouched.
+ * It calls no hipMalloc, hipFree or allocating routine. DRPF_EWORKSPACE if the solve needs more
+ * than 32 MiB of scratch: (nx/2 + 1) * ny * nz complex elements of the chosen grid. Every call on
+ * one GPU uses that GPU's one array: calls that overlap on a GPU (on different streams, or from
+ * several threads) race and must be serialised by the caller. */
 int drpf_helmholtz_solve_static(drpf_grid* g, int which_grid, int bc, double coeff, double shift,
                                 const void* rhs, const void* wall_data, void* x, void* stream);
 

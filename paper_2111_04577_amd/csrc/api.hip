@@ -178,10 +178,9 @@ Offsets layout(const drpf_params& p, const Dims& F, const Dims& C) {
 
 }  // namespace
 
-// Scratch of the allocation-free solve (drpf_helmholtz_solve_static): the spectral buffer
-// and the right-hand side with the wall terms of one solve, for grids up to this size. Each
-// GPU holds its own copy until the process ends; in host code its name is only a stand-in for
-// the device address, which scratch_ptr() looks up once per device.
+// Scratch of the allocation-free solve (drpf_helmholtz_solve_static): the spectral buffer of
+// one solve, for grids up to this size. Each GPU holds its own copy until the process ends; in host
+// code its name is only a stand-in for the device address, which scratch_ptr() looks up once per device.
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
@@ -1154,8 +1153,7 @@ int drpf_helmholtz_solve_static(drpf_grid* g, int which_grid, int bc, double coe
   if (rc) return rc;
   const Dims& d = which_grid == DRPF_GRID_FINE ? g->F : g->C;
   const size_t es = g->p.precision == 32 ? 4 : 8;
-  const size_t sbytes = (d.spec() * 2 * es + 255) & ~(size_t)255;
-  const size_t need = sbytes + (wall_data ? d.cells() * es : 0);
+  const size_t need = d.spec() * 2 * es;
   if (need > kStaticScratchBytes)
     return fail(DRPF_EWORKSPACE, "drpf_helmholtz_solve_static: the solve needs " + std::to_string(need) +
                                      " bytes of scratch, above the static limit of " +
@@ -1163,11 +1161,10 @@ int drpf_helmholtz_solve_static(drpf_grid* g, int which_grid, int bc, double coe
   void* scr = nullptr;
   const int pc = scratch_ptr(&scr);
   if (pc) return pc;
-  char* base = (char*)scr;
   hipStream_t st = (hipStream_t)stream;
   return g->p.precision == 64
-             ? helmholtz_impl<double>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, base)
-             : helmholtz_impl<float>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, base);
+             ? helmholtz_impl<double>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, scr)
+             : helmholtz_impl<float>(g, which_grid, bc, coeff, shift, rhs, wall_data, x, st, scr);
 }
 
 int drpf_helmholtz_solve(drpf_grid* g, int which_grid, int bc, double coeff, double shift,
