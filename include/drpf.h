@@ -22,7 +22,7 @@
  *     Wi, beta, static contact angles (eq. NS16, measured through the drop, phase
  *     phi = +1), rho_ratio = drop/ambient density, mu_ratio = drop/ambient viscosity.
  *   - Scalars are double on the host. Device arrays hold double when precision == 64 and
- *     float when precision == 32.
+ *     float when precision == 32, aligned to their elements (the workspaces: to 256 bytes).
  *
  * Memory ownership: the caller allocates every device buffer (state arrays, the workspace)
  * and keeps it valid until the work queued on the stream has completed. The library never

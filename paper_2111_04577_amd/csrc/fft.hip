@@ -21,6 +21,22 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// Pair e (even, odd) of a row of reals in a caller's array, which may be aligned to its elements only:
+// one access of two elements all the same, which the hardware takes at any element.
+template <typename T>
+struct __attribute__((packed, aligned(alignof(T)))) PairU {
+  T re, im;
+};
+template <typename T>
+__device__ __forceinline__ cx<T> ld_pair(const T* row, size_t e) {
+  const PairU<T> v = reinterpret_cast<const PairU<T>*>(row)[e];
+  return mk<T>(v.re, v.im);
+}
+template <typename T>
+__device__ __forceinline__ void st_pair(T* row, size_t e, cx<T> v) {
+  reinterpret_cast<PairU<T>*>(row)[e] = PairU<T>{v.re, v.im};
+}
+
 // Wall data of a solve, read with the rows of its right-hand side: rows of the layers zb and zt
 // lose c times the row of the bottom or top wall layer.
 template <typename T>
@@ -32,13 +48,12 @@ struct WallRows {
   __device__ __forceinline__ cx<T> apply(cx<T> v, int r, int k, int M, int Ny, int lny) const {
     const int z = r >> lny, y = r & (Ny - 1);
     if (z != zb && z != zt) return v;
-    const cx<T>* row = reinterpret_cast<const cx<T>*>(w);
     if (z == zb) {
-      const cx<T> a = row[(size_t)y * M + k];
+      const cx<T> a = ld_pair(w, (size_t)y * M + k);
       v = mk<T>(v.re - c * a.re, v.im - c * a.im);
     }
     if (z == zt) {
-      const cx<T> a = row[(size_t)(Ny + y) * M + k];
+      const cx<T> a = ld_pair(w, (size_t)(Ny + y) * M + k);
       v = mk<T>(v.re - c * a.re, v.im - c * a.im);
     }
     return v;
@@ -46,7 +61,8 @@ struct WallRows {
 };
 
 // ---- x pass, forward (r2c) -------------------------------------------------------------
-// WALL: the rows next to the walls take the wall data of a solve. A block holds lpb rows (FftPlan line layout), T = M / P threads per row.
+// WALL: the rows next to the walls take the wall data of a solve. A block holds lpb rows (FftPlan
+// line layout), T = M / P threads per row.
 template <typename T, int LOGM, bool WALL = false>
 __global__ void __launch_bounds__(kBlock) k_fft_x_fwd(const T* __restrict__ in0,
                                                       const T* __restrict__ in1,
@@ -67,10 +83,9 @@ __global__ void __launch_bounds__(kBlock) k_fft_x_fwd(const T* __restrict__ in0,
   const int field = line0 / lines_per_field;
   const T* in = field == 0 ? in0 : (field == 1 ? in1 : in2);
   const T* src = in + (size_t)(line0 - field * lines_per_field) * (2 * M);
-  // a row of 2M reals read as M (even, odd) pairs: rows start at even offsets of arrays
-  // aligned to at least 16 bytes, so each pair is one aligned load
+  // a row of 2M reals read as M (even, odd) pairs
   for (int e = threadIdx.x; e < nl * M; e += blockDim.x) {
-    cx<T> v = reinterpret_cast<const cx<T>*>(src)[e];
+    cx<T> v = ld_pair(src, e);
     if (WALL) v = wr.apply(v, line0 + (e >> LOGM), e & (M - 1), M, Ny, __ffs(Ny) - 1);
     buf[(e >> LOGM) * F::LS + F::pad(e & (M - 1))] = v;
   }
@@ -146,13 +161,13 @@ __global__ void __launch_bounds__(kBlock) k_fft_x_inv(const cx<T>* __restrict__ 
   if (add != nullptr) {
     add += (size_t)(line0 - field * lines_per_field) * (2 * M);
     for (int e = threadIdx.x; e < nl * M; e += blockDim.x) {
-      const cx<T> a = reinterpret_cast<const cx<T>*>(add)[e];
+      const cx<T> a = ld_pair(add, e);
       const cx<T> v = buf[(e >> LOGM) * F::LS + F::pad(e & (M - 1))];
-      reinterpret_cast<cx<T>*>(dst)[e] = mk<T>(a.re + v.re, a.im + v.im);
+      st_pair(dst, e, mk<T>(a.re + v.re, a.im + v.im));
     }
   } else {
     for (int e = threadIdx.x; e < nl * M; e += blockDim.x)
-      reinterpret_cast<cx<T>*>(dst)[e] = buf[(e >> LOGM) * F::LS + F::pad(e & (M - 1))];
+      st_pair(dst, e, buf[(e >> LOGM) * F::LS + F::pad(e & (M - 1))]);
   }
 }
 
@@ -226,10 +241,9 @@ __global__ void __launch_bounds__(kBlock) k_fft_x_fwd_rt(const T* __restrict__ i
   const int field = line0 / lines_per_field;
   const T* in = field == 0 ? in0 : (field == 1 ? in1 : in2);
   const T* src = in + (size_t)(line0 - field * lines_per_field) * N;
-  // a row of N reals read as N/2 (even, odd) pairs: rows start at even offsets of arrays
-  // aligned to at least 16 bytes, so each pair is one aligned load
+  // a row of N reals read as N/2 (even, odd) pairs
   for (int e = threadIdx.x; e < nl * M; e += blockDim.x) {
-    cx<T> v = reinterpret_cast<const cx<T>*>(src)[e];
+    cx<T> v = ld_pair(src, e);
     if (WALL) v = wr.apply(v, line0 + (e >> logM), e & (M - 1), M, Ny, __ffs(Ny) - 1);
     buf[e] = v;
   }
@@ -298,11 +312,11 @@ __global__ void __launch_bounds__(kBlock) k_fft_x_inv_rt(const cx<T>* __restrict
   if (add != nullptr) {
     add += (size_t)(line0 - field * lines_per_field) * N;
     for (int e = threadIdx.x; e < nl * M; e += blockDim.x) {
-      const cx<T> a = reinterpret_cast<const cx<T>*>(add)[e];
-      reinterpret_cast<cx<T>*>(dst)[e] = mk<T>(a.re + buf[e].re, a.im + buf[e].im);
+      const cx<T> a = ld_pair(add, e);
+      st_pair(dst, e, mk<T>(a.re + buf[e].re, a.im + buf[e].im));
     }
   } else {
-    for (int e = threadIdx.x; e < nl * M; e += blockDim.x) reinterpret_cast<cx<T>*>(dst)[e] = buf[e];
+    for (int e = threadIdx.x; e < nl * M; e += blockDim.x) st_pair(dst, e, buf[e]);
   }
 }
 
@@ -463,11 +477,11 @@ __global__ void __launch_bounds__(1024)
   if (add != nullptr) {
     add += (size_t)z * Ny * N;
     for (int e = threadIdx.x; e < n; e += blockDim.x) {
-      const cx<T> a = reinterpret_cast<const cx<T>*>(add)[e];
-      reinterpret_cast<cx<T>*>(dst)[e] = mk<T>(a.re + A[e].re, a.im + A[e].im);
+      const cx<T> a = ld_pair(add, e);
+      st_pair(dst, e, mk<T>(a.re + A[e].re, a.im + A[e].im));
     }
   } else {
-    for (int e = threadIdx.x; e < n; e += blockDim.x) reinterpret_cast<cx<T>*>(dst)[e] = A[e];
+    for (int e = threadIdx.x; e < n; e += blockDim.x) st_pair(dst, e, A[e]);
   }
 }
 
