@@ -31,13 +31,14 @@
  *
  * Streams: every call that takes a stream queues its work asynchronously on it (a
  * hipStream_t passed as void*; NULL is the default stream), except drpf_observables, which
- * synchronises that stream before returning. Calls on one grid must not overlap. With the
- * log-conformation form (constitutive 1) drpf_step runs the polymer update of every step but
- * the last of a call on a stream the library creates (default priority, created by
+ * synchronises that stream before returning. Calls on one grid must not overlap. Where the
+ * polymer update is bound by arithmetic (the log-conformation form, constitutive 1; the stress
+ * form with WENO-Z, advection 1, in FP64 up to 2^20 flow cells) drpf_step runs the update of every
+ * step but the last of a call on a stream the library creates (default priority, created by
  * drpf_init_grid, released by drpf_destroy), forked from the caller's stream by an event after
  * the velocity correction and joined back by an event before the next step's momentum
- * right-hand side and before drpf_step returns: the caller's stream
- * orders all of the call's work as if it had run on it alone.
+ * right-hand side and before drpf_step returns: the caller's stream orders all of the call's
+ * work as if it had run on it alone.
  *
  * Errors: every call returns one of the DRPF_* codes below; drpf_last_error() gives a
  * thread-local message for the last failure on the calling thread.

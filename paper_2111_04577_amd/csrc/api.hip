@@ -67,6 +67,21 @@ Dims fine_dims(const drpf_params& p) {
   return make_dims(r * p.nx, ry * p.ny, r * p.nz, p.lx, p.ly, p.lz);
 }
 
+// Whether the polymer update is worth a stream of its own. Bound by arithmetic are the
+// log-conformation (its eigensolves) and the stress form with WENO-Z (36 reconstructions a cell); the
+// stress form with central advection is bound by memory, as is the pass it would overlap. In FP64
+// the WENO-Z stages of more than 2^20 cells lose more to that pass, with which they then share HBM, than
+// they hide. Eight steps in ms without and with the overlap: log-conformation with WENO-Z, 128 x 128 x
+// 64 coarse cells, 4.70 / 4.21 FP32, 7.51 / 7.19 FP64; stress form with WENO-Z, the same grid, 4.03 /
+// 3.81 FP32, 6.89 / 6.65 FP64, 256 x 1 x 128 0.70 / 0.69, 0.82 / 0.77, 256 x 128 x 64 7.59 / 7.41,
+// 13.14 / 13.48, 256 x 256 x 128 29.0 / 28.7, 54.2 / 55.6; stress form, central, 256 x 256 x 128
+// 16.81 / 16.85, 31.7 / 31.8, 32 x 32 x 16 (four steps) 0.343 / 0.385 FP32.
+bool overlaps_update(const drpf_params& p, const Dims& C) {
+  if (!p.viscoelastic) return false;
+  if (p.constitutive == 1) return true;
+  return p.advection == 1 && (p.precision == 32 || C.cells() <= (size_t)1 << 20);
+}
+
 // Scheme constants (own derivation of the paper's formulas; see the header of this file).
 StepConsts make_consts(const drpf_params& p, bool first) {
   StepConsts c;
@@ -216,8 +231,8 @@ struct drpf_grid {
   Offsets o;
   // adjoint workspace (FP64 grids), attached by drpf_adjoint_attach
   char* aws = nullptr;
-  // log-conformation grids: the polymer update of a step that another step of the same call
-  // follows runs on a stream of the library's own, forked from the caller's stream after the
+  // grids whose polymer update is bound by arithmetic (overlaps_update): the update of a step
+  // that another step of the same call follows runs on a stream of the library's own, forked from the caller's stream after the
   // velocity correction and joined before the next step's momentum right-hand side (the next
   // step's Cahn-Hilliard pass overlaps it)
   hipStream_t side = nullptr;
@@ -581,14 +596,11 @@ template <typename T>
 int step_impl(drpf_grid* g, drpf_state* s, int nsteps, hipStream_t st) {
   const bool ve = g->p.viscoelastic != 0;
   const int every = g->p.check_finite_every;
-  // The log-conformation update, which is bound by arithmetic, overlaps the next step's
-  // Cahn-Hilliard pass, which is bound by memory (except while per-kernel events are being
-  // recorded: they time one stream). A fork and join costs about 25 us of host time and two
-  // queue hand-overs, so it is not made for the last step of a call, where nothing follows to
-  // overlap with, nor for the stress form, whose update is bound by memory too. Eight steps with
-  // and without it, 128 x 128 x 64 coarse cells, log-conformation with WENO-Z: 5.41 / 6.07 ms FP32,
-  // 9.44 / 10.04 ms FP64; 256 x 256 x 128, stress form: 16.85 / 16.81 and 31.8 / 31.7 ms; one step
-  // of the former 0.780 / 0.759 ms, four steps of 32 x 32 x 16, stress form: 0.385 / 0.343 ms.
+  // An update that is bound by arithmetic (overlaps_update) overlaps the next step's Cahn-Hilliard
+  // pass, which is bound by memory (except while per-kernel events are being recorded: they time
+  // one stream). A fork and join costs about 25 us of host time and two queue hand-overs, so it is
+  // not made for the last step of a call, where nothing follows to overlap with: one step of
+  // 128 x 128 x 64 coarse cells, log-conformation with WENO-Z, takes 0.780 ms with it, 0.759 without.
   const bool can_overlap = g->side != nullptr && !g->prof;
   // whatever happens, the caller's stream ends up after the last polymer update
   struct Join {
@@ -1022,7 +1034,7 @@ int drpf_init_grid(const drpf_params* p, void* d_workspace, size_t bytes, void* 
     void* scr = nullptr;
     rc = scratch_ptr(&scr);
   }
-  if (!rc && p->viscoelastic && p->constitutive == 1) {
+  if (!rc && overlaps_update(*p, g->C)) {
     // the stream the polymer update overlaps on (default priority) and its fork/join events
     hipError_t e = hipStreamCreateWithFlags(&g->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&g->ev_fork, hipEventDisableTiming);
