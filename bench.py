@@ -436,7 +436,8 @@ def accuracy_vs_oracle(drpf, W, cfg, nsteps, oracle_state):
 def ingest_pmc(fetch_csv, write_csv, out_json, workload):
     """rocprofv3 --pmc counter_collection.csv files (one run with FETCH_SIZE, one with
     WRITE_SIZE, each of `bench.py --copy-calibration` on one workload) -> HBM bytes per launch
-    of every kernel on that workload, merged into out_json under kernel/precision/workload.
+    of every kernel on that workload, in out_json under kernel/precision/workload in place of
+    that precision's and workload's entries there.
     Each counter (KiB per dispatch) is scaled by (copy bytes) / (the same counter read on the
     1 GiB device copy of that run). Kernels launched on both grids are told apart by their
     grid size (the larger is the fine grid)."""
@@ -511,6 +512,9 @@ def ingest_pmc(fetch_csv, write_csv, out_json, workload):
                                                              "dispatches": len(vals), "name": name})
         ent["fetch_bytes"] += fb
         ent["write_bytes"] += wb
+    # a workload's entries are replaced as a whole: kernels that no longer run there drop out
+    forms = {key.split("/", 1)[1] for key in acc}
+    out = {key: ent for key, ent in out.items() if key.partition("/")[2] not in forms}
     for key, ent in acc.items():
         out[key] = {"bytes_per_launch": round(ent["fetch_bytes"] + ent["write_bytes"]),
                     "fetch_bytes": round(ent["fetch_bytes"]), "write_bytes": round(ent["write_bytes"]),

@@ -1,7 +1,10 @@
 // Right-hand side of the fused Cahn-Hilliard solve and its forward x transform in one pass:
 // Q - L_N b of eqs. NS25-NS34 (stencil_ch.hip, ch_rhs) formed row by row, transformed in LDS
 // (r2c, as k_fft_x_fwd) and written in the spectral layout, so that the right-hand side never
-// goes through memory (2 N_f of the 5 N_f + 6 N_c words of the two passes).
+// goes through memory (2 N_f of the 5 N_f + 6 N_c words of the two passes). The halo rows give part of
+// that back: a block of TY rows reads TY + 2 of phi^n and phi^{n-1}. At 512 columns in FP64 it holds
+// two rows and reads four, 2.75 GB a launch by counter where the pass's own words are 2.02 GB and the
+// two passes moved 3.19; in FP32, where it holds four, 1.08, 1.01 and 1.57 GB.
 //
 // A block owns TY whole x rows and marches up KB layers. Each thread owns 16 bytes of a row (4
 // columns in FP32, 2 in FP64): every load of the march is a 16-byte load, the x neighbours are the

@@ -1218,8 +1218,8 @@ hipError_t launch_zpass_ns(const Dims& d, const Tables<T>& tb, cx<T>* spec4, con
   // velocity solves, g / a = gamma0 hz^2 / (dt nu_m), goes to zero, the walls' 1 - rho^2N does too and
   // the recurrences lose eps / sqrt(g / a). Error of the velocity, reduction against recurrences:
   // 32 rows 1.1e-14, 3.4e-15 at 1e-3, 1.1e-14, 4.3e-14 at 1e-4, 1.2e-15, 1.6e-11 at 1e-10; 512 rows
-  // 1.1e-13, 5.3e-15 at 1e-3, 3.4e-12, 5.4e-12 at 1e-6, 1.2e-13, 2.1e-11 at 1e-10. The runs of
-  // interest are at 0.06 and up. The pressure, whose walls carry no flux, is closer by recurrences at any gap.
+  // 1.1e-13, 5.3e-15 at 1e-3, 3.4e-12, 5.4e-12 at 1e-6, 1.2e-13, 2.1e-11 at 1e-10. The workloads'
+  // gaps are 0.04 and up. The pressure, whose walls carry no flux, is closer by recurrences at any gap.
   const double gap = c.gamma0 / c.dt * d.hz * d.hz / c.nu_m;
   if constexpr (sizeof(T) == 8)
     if (d.ny > 1 && gap >= 1e-3 && (d.nz >= 128 || (d.nz >= 32 && lines * d.nz >= 1 << 17))) {

@@ -3,10 +3,10 @@ right-hand side and x transform (the hand-over of its two layer slots and of the
 batches of four layers) and the single-resolution restricted set (its layer rings). A block marches
 layers / (resident blocks per column) of them, so this takes many columns: a small periodic problem
 repeated along y (2D: x), whose solution is the small one's repeated, against the FP64 oracle on the small
-one. In FP64 every case but the smaller repeat asks for two to sixteen times the threads that the card
-holds at once. Two steps (start-up and
-BDF2): FP64 1e-10 of the largest entry (round-off of a stiff solve, as in every parity test here),
-FP32 phi 1e-4 (its 1e-6 of the fourth-order right-hand side over two steps)."""
+one. In FP64 every case that takes a march asks for two to sixteen times the threads that the card holds
+at once. Two steps
+(start-up and BDF2): FP64 1e-10 of the largest entry (round-off of a stiff solve, as in every parity
+test here), FP32 phi 1e-4 (its 1e-6 of the fourth-order right-hand side over two steps)."""
 from __future__ import annotations
 
 import numpy as np
